@@ -2,16 +2,17 @@
 //
 // Forward: one workgroup per tile; each wave owns an 8x8 pixel block, one
 // lane per pixel. The tile's instances are staged through LDS in batches of
-// one record per lane; each wave then keeps only the staged splats whose
-// covered pixel rect meets its block and walks them. For the Pluecker
+// one record per lane; each wave then lists, for each 4x4 part of its block,
+// the staged splats that can reach the part, and its four parts walk their
+// lists side by side. For the Pluecker
 // direction d and moment m of its pixel ray in splat space, rho^2 =
 // |m|^2/|d|^2 (Eq. rho-pluecker), alpha = min(alpha_max, o exp(-rho^2/2)),
 // and for fragments with alpha >= tau_K the view depth of the
 // maximum-density point z = (M T [(d x m)/|d|^2; 1])_z (Sec. 3.3); since d
 // and m are affine in the pixel offset, |d|^2, |m|^2 and R3 . (d x m) are
 // quadratics in it, staged per (tile, splat) and evaluated per pixel. The
-// fragments enter a register core of K (depth, list position) entries kept
-// sorted by a median-of-three / select shift. Every fragment is
+// fragments enter a register core of K (depth, list position) keys kept
+// sorted by minima and maxima of doubles. Every fragment is
 // added to running sums (sum alpha, sum alpha rgb, prod (1 - alpha)); at
 // the end the core members are taken back out of them, which leaves the
 // order-independent tail of everything that never entered the core or fell
@@ -23,10 +24,8 @@
 // fragment of the pixel (Sec. 3.3, last paragraph). Then each wave takes 64
 // of the tile's instances, one per lane, and loops over the tile's pixels
 // (skipping 8x8 blocks no lane's rect touches), recomputing rho^2 and alpha
-// (|d|^2 and |m|^2 as sums of squares along each pixel row, which round a
-// little differently from the forward's per-tile forms: a fragment within
-// rounding of the cutoff, whose alpha is tau_alpha, may be judged
-// differently; core members, with alpha >= tau_K, never are). Because d
+// (from the forward's staged forms in its operation order: the same bits, so
+// exactly the fragments that the forward blended). Because d
 // and m are affine in the pixel offset (lx, ly), the gradient w.r.t. their
 // 18 affine coefficients follows
 // from six moments of dL/d(rho^2)-weights per vector (sum of w, w lx, w ly,
@@ -39,6 +38,8 @@
 #include "common.h"
 
 namespace htgs {
+
+typedef float float4v __attribute__((ext_vector_type(4)));   // one 16-byte LDS read
 
 constexpr float kNegHalfLog2e = -0.72134752044448170368f;  // -1 / (2 ln 2)
 
@@ -61,11 +62,9 @@ __device__ __forceinline__ float rcp_fast(float x) { return __builtin_amdgcn_rcp
 enum FwdStage {
   F_QD = 0,           // |d|^2
   F_QM = 6,           // |m|^2: |r|^2, R11, R12, k1, R22, k2
-  F_RC = 12, F_O = 13, F_MUZ = 14, F_R = 15,
-  F_QZ = 16,          // R3 . (d x m)
-  F_G = 22, F_B = 23,
-  F_BB = 24,          // covered pixel rect relative to the tile's first pixel
-  F_FLOATS = 28, F_TEST4 = 4   // float4s read for the cutoff test and alpha
+  F_RC = 12, F_O = 13, F_R = 14, F_G = 15, F_B = 16, F_MUZ = 17,
+  F_QZ45 = 18, F_QZ = 20,   // R3 . (d x m): its last two coefficients, its first four
+  F_FLOATS = 24, F_TEST4 = 4   // float4s read for the cutoff test and alpha
 };
 
 __device__ __forceinline__ void cross_f(const float a[3], const float b[3], float c[3]) {
@@ -157,9 +156,9 @@ __device__ __forceinline__ void stage_fwd(const float *__restrict__ rec, int cx2
   q[F_QZ + 2] = triple2(R3, D0, Mv, Dv, M0);
   cross_f(Du, Mu, c);
   q[F_QZ + 3] = dot_f(R3, c);
-  q[F_QZ + 4] = triple2(R3, Du, Mv, Dv, Mu);
+  q[F_QZ45 + 0] = triple2(R3, Du, Mv, Dv, Mu);
   cross_f(Dv, Mv, c);
-  q[F_QZ + 5] = dot_f(R3, c);
+  q[F_QZ45 + 1] = dot_f(R3, c);
   q[F_RC] = rec[R_RC];
   q[F_O] = rec[R_O];
   q[F_MUZ] = rec[R_MUZ];
@@ -192,15 +191,10 @@ __device__ __forceinline__ float eval_mm(const float *c, const PixQ &u) {
   return fmaf(s1, s1, fmaf(s2, s2, c[0]));
 }
 
-// min(x, a) as a compare and a select (fminf canonicalizes its operands
-// first, which costs an instruction per call in the raster loops).
-__device__ __forceinline__ float min_sel(float x, float a) {
-  return x <= a ? x : a;
-}
-
-// alpha = min(alpha_max, o exp(-rho^2 / 2)) with rho^2 = mm / dd.
+// alpha = min(alpha_max, o exp(-rho^2 / 2)) with rho^2 = mm / dd (a median
+// with 0: fminf canonicalizes its operands first).
 __device__ __forceinline__ float frag_alpha(float o, float mm, float inv, float amax) {
-  return min_sel(o * exp2_fast((mm * inv) * kNegHalfLog2e), amax);
+  return __builtin_amdgcn_fmed3f(o * exp2_fast((mm * inv) * kNegHalfLog2e), 0.f, amax);
 }
 
 __device__ __forceinline__ bool is_fragment(float dd, float mm, float rc) {
@@ -289,6 +283,233 @@ __device__ __forceinline__ bool rect_meets_block(const float *bb, int bx, int by
 // ---------------------------------------------------------------------------
 // Forward
 // ---------------------------------------------------------------------------
+// A wave owns an 8x8 pixel block, one lane per pixel, cut into kParts parts
+// of 4 columns and kPartRows rows, 64 / kParts consecutive lanes each. Every
+// part walks a list of its own, of the staged splats that can reach it, so a
+// step of the wave handles up to kParts different splats. The walk is bound
+// by VALU issue, and a step costs the same whatever share of its lanes hold
+// a fragment: with one list per block 64% of the lanes of the 1080p frame
+// (1M Gaussians, K = 8, 8x8 tiles, 205 splats per tile), with four lists 69%
+// in 0.71 times the steps. Eight lists of 4x2 pixels shorten them further,
+// but their rows' reads meet in the LDS banks and their lists cost more to
+// build: 444 us against 419 for the launch at 1080p, 7.05 ms against 6.98 on
+// a 3840x2160 frame of 6M Gaussians.
+constexpr int kParts = 4;
+constexpr int kPartRows = 16 / kParts;
+constexpr int kPartLanes = 64 / kParts;
+__device__ __forceinline__ int part_x(int lane) {
+  return (lane & 3) | ((lane / kPartLanes) & 1) * 4;
+}
+__device__ __forceinline__ int part_y(int lane) {
+  return ((lane % kPartLanes) >> 2) + (lane / (2 * kPartLanes)) * kPartRows;
+}
+
+// Parts of a TW x TH tile that a staged splat can reach: bit kParts b + p for
+// part p of 8x8 block b. A pixel row of a part is missed when the smallest
+// |m|^2 over its columns (X taken as continuous between the first and the
+// last) exceeds rho_c times the largest |d|^2 over the tile (a bound from the
+// coefficients' magnitudes; |d|^2 hardly changes over a tile). The slack
+// (2e-6 of the terms of s1 and s2, 1e-4 of the bound) is far above the
+// rounding of the per-pixel test, so no part with a fragment is left out.
+template <int TW, int TH>
+__device__ __forceinline__ uint32_t part_mask(const float *q) {
+  constexpr int QX = TW / 4, QY = TH / kPartRows, BX = TW / 8, BY = 8 / kPartRows;
+  const float hx = 0.5f * (float)(TW - 1), hy = 0.5f * (float)(TH - 1);
+  const float *d = q + F_QD, *m = q + F_QM;
+  const float ddmax = fmaf(hx, fabsf(d[1]), fmaf(hy, fabsf(d[2]), fmaf(hx * hy, fabsf(d[4]),
+                      fmaf(hx * hx, d[3], fmaf(hy * hy, d[5], d[0])))));
+  const float lim = fmaf(q[F_RC] * ddmax, 1.0001f, -m[0]);
+  const float ax = fabsf(m[1]);
+  const float h = fmaf(1.5f, ax, 2e-6f * fmaf(hx, ax, fmaf(hy, fabsf(m[2]), fabsf(m[3]))));
+  const float e2 = 2e-6f * fmaf(hy, fabsf(m[4]), fabsf(m[5]));
+  uint32_t mask = 0u;
+#pragma unroll
+  for (int qy = 0; qy < QY; ++qy) {
+    float best[QX];   // smallest s1^2 + s2^2 - lim over the part's rows
+#pragma unroll
+    for (int r = 0; r < kPartRows; ++r) {
+      const float y = (float)(kPartRows * qy + r) - hy;
+      const float s2 = fmaxf(fabsf(fmaf(m[4], y, m[5])) - e2, 0.f);
+      const float a = fmaf(m[2], y, m[3]);
+      const float c = fmaf(s2, s2, -lim);
+#pragma unroll
+      for (int qx = 0; qx < QX; ++qx) {
+        const float s1 = fmaxf(fabsf(fmaf(m[1], (float)(4 * qx) + 1.5f - hx, a)) - h, 0.f);
+        const float v = fmaf(s1, s1, c);
+        best[qx] = r == 0 ? v : fminf(best[qx], v);
+      }
+    }
+#pragma unroll
+    for (int qx = 0; qx < QX; ++qx) {
+      const int bit = kParts * ((qy / BY) * BX + (qx >> 1)) + 2 * (qy % BY) + (qx & 1);
+      if (!(best[qx] > 0.f)) mask |= 1u << bit;   // (kept where a form is not finite)
+    }
+  }
+  return mask;
+}
+
+// Blocks of the tile whose pixels meet the covered pixel rect (b0, b1: the
+// record's packed corners), kParts bits each. One-block tiles take them all.
+template <int TW, int TH>
+__device__ __forceinline__ uint32_t rect_block_mask(uint32_t b0, uint32_t b1, int px0, int py0) {
+  constexpr uint32_t kAll = (1u << kParts) - 1u;
+  if constexpr (TW * TH == 64) return kAll;
+  uint32_t mask = 0u;
+  const int x0 = (int)(b0 & 0xffffu) - px0, y0 = (int)(b0 >> 16) - py0;
+  const int x1 = (int)(b1 & 0xffffu) - px0, y1 = (int)(b1 >> 16) - py0;
+#pragma unroll
+  for (int b = 0; b < TW * TH / 64; ++b) {
+    const int bx = (b % (TW / 8)) * 8, by = (b / (TW / 8)) * 8;
+    if (x1 >= bx && x0 <= bx + 7 && y1 >= by && y0 <= by + 7) mask |= kAll << (kParts * b);
+  }
+  return mask;
+}
+
+// A batch of staged splats in LDS and the parts' lists of them (byte offsets
+// of the rows).
+constexpr int kStageBytes = F_FLOATS * 4;
+template <int TW, int TH, int NBATCH>
+struct FwdLds {
+  static constexpr int kWaves = TW * TH / 64;
+  // one row per splat; the last row is all zeros (|d|^2 = 0: no fragment)
+  float4 stage[(NBATCH + 1) * (F_FLOATS / 4)];
+  union {
+    uint16_t list[kWaves][kParts][NBATCH];
+    uint2 fill[kWaves][kParts * NBATCH / 4];
+  };
+  uint32_t mask[kWaves > 1 ? NBATCH : 1];
+};
+
+// Stages one splat; returns the parts it can reach.
+template <int TW, int TH, int NBATCH>
+__device__ __forceinline__ uint32_t stage_splat(FwdLds<TW, TH, NBATCH> &L, int r,
+                                                const float *__restrict__ recs, uint32_t gid,
+                                                int px0, int py0) {
+  float rec[kRecFloats];
+  load_record(recs, gid, rec);
+  float st[F_FLOATS];
+  stage_fwd(rec, 2 * px0 + TW - 1, 2 * py0 + TH - 1, st);
+#pragma unroll
+  for (int k = 0; k < F_FLOATS / 4; ++k)
+    L.stage[r * (F_FLOATS / 4) + k] =
+        make_float4(st[4 * k], st[4 * k + 1], st[4 * k + 2], st[4 * k + 3]);
+  return part_mask<TW, TH>(st) &
+         rect_block_mask<TW, TH>(__float_as_uint(rec[R_BB0]), __float_as_uint(rec[R_BB1]), px0, py0);
+}
+
+// Adds the staged splat j of each lane (part bits m of this wave's block; 0
+// past the batch) to the wave's lists; n: the lists' lengths. Called by all
+// 64 lanes.
+template <int NBATCH>
+__device__ __forceinline__ void extend_lists(uint16_t (*list)[NBATCH], int j, uint32_t m, int *n) {
+#pragma unroll
+  for (int p = 0; p < kParts; ++p) {
+    const bool hit = (m & (1u << p)) != 0u;
+    const uint64_t mk = __ballot(hit);
+    const uint32_t at = __builtin_amdgcn_mbcnt_hi(
+        (uint32_t)(mk >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk, (uint32_t)n[p]));
+    if (hit) list[p][at] = (uint16_t)(j * kStageBytes);
+    n[p] += __popcll(mk);
+  }
+}
+
+// Stages up to NBATCH splats of a tile's list (cnt of them from vals on) and
+// builds this wave's lists; returns the longest one's length, an even number
+// (the lists are padded with the zero row). All threads of the workgroup.
+template <int TW, int TH, int NBATCH>
+__device__ __forceinline__ int stage_batch(FwdLds<TW, TH, NBATCH> &L,
+                                           const float *__restrict__ recs,
+                                           const uint32_t *__restrict__ vals, int cnt, int px0,
+                                           int py0, int wave, int lane) {
+  constexpr int NT = TW * TH;
+  int n[kParts];
+#pragma unroll
+  for (int p = 0; p < kParts; ++p) n[p] = 0;
+  constexpr uint32_t kZeroRow = (uint32_t)(NBATCH * kStageBytes);
+  constexpr uint32_t kZero2 = kZeroRow | (kZeroRow << 16);
+  static_assert(kZeroRow < 65536u, "row offsets are 16 bits");
+#pragma unroll
+  for (int i = 0; i < kParts * NBATCH / 4; i += 64)
+    if (i + lane < kParts * NBATCH / 4) L.fill[wave][i + lane] = make_uint2(kZero2, kZero2);
+  __builtin_amdgcn_wave_barrier();
+  if constexpr (NT == 64) {
+#pragma unroll
+    for (int r0 = 0; r0 < NBATCH; r0 += 64) {
+      const int r = r0 + lane;
+      uint32_t m = 0u;
+      if (r < cnt) m = stage_splat(L, r, recs, vals[r], px0, py0);
+      extend_lists<NBATCH>(L.list[0], r, m, n);
+    }
+    __syncthreads();
+  } else {
+    static_assert(NBATCH == NT, "one record per thread");
+    const int r = wave * 64 + lane;
+    if (r < cnt) L.mask[r] = stage_splat(L, r, recs, vals[r], px0, py0);
+    __syncthreads();
+    for (int j0 = 0; j0 < cnt; j0 += 64) {
+      const int j = j0 + lane;
+      const uint32_t m = j < cnt ? L.mask[j] >> (kParts * wave) : 0u;
+      extend_lists<NBATCH>(L.list[wave], j, m, n);
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  int longest = 0;
+#pragma unroll
+  for (int p = 0; p < kParts; ++p) longest = max(longest, n[p]);
+  return (longest + 1) & ~1;
+}
+
+// Core keys: depth in the high word, list position and alpha slot in the
+// low word, as a double. Depths are positive and at most infinity (as
+// float32 bits, never a NaN of the double), so doubles compare like (depth,
+// position), and one minimum and one maximum per entry insert a fragment.
+__device__ __forceinline__ double core_key(uint32_t hi, uint32_t lo) {
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ uint32_t key_hi(double k) {
+  return (uint32_t)((unsigned long long)__double_as_longlong(k) >> 32);
+}
+__device__ __forceinline__ uint32_t key_lo(double k) {
+  return (uint32_t)(unsigned long long)__double_as_longlong(k);
+}
+// (fmin and fmax would canonicalize their operands first)
+__device__ __forceinline__ double key_min(double a, double b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ double key_max(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
+// Inserts x into the sorted keys; the last one drops out. (Four minima ahead
+// of their maxima: no instruction waits for the one before it.)
+template <int KMAX>
+__device__ __forceinline__ void core_insert(double *key, double x) {
+#pragma unroll
+  for (int g = KMAX - 1; g >= 1; g -= 4) {
+    double m[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (g - i >= 1) m[i] = key_min(key[g - i], x);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (g - i >= 1) key[g - i] = key_max(key[g - i - 1], m[i]);
+  }
+  key[0] = key_min(key[0], x);
+}
+
+constexpr int log2_of(int x) { return x <= 1 ? 0 : 1 + log2_of(x / 2); }
+
+// The wave's fragments to the forward's counter. All 64 lanes.
+__device__ __forceinline__ void add_fragments(const Ws &w, uint32_t n, int lane) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) n += (uint32_t)__shfl_xor((int)n, off, 64);
+  if (lane == 0 && n) count_add(w.frags, (unsigned long long)n);
+}
+
 // One tile. EXACT: K == KMAX, known at compile time.
 template <int KMAX, int TW, int TH, int BM, bool EXACT>
 __device__ __forceinline__ void fwd_tile(const TileInfo &ti, const Ws &w, const ViewSet &vs,
@@ -298,169 +519,111 @@ __device__ __forceinline__ void fwd_tile(const TileInfo &ti, const Ws &w, const 
   constexpr int NBATCH = NT * BM;   // records staged per batch
   constexpr int NW = NT / 64;       // waves, one 8x8 block each
   constexpr int BX = TW / 8;
-  constexpr int SV = F_FLOATS / 4;
-  __shared__ float4 s_stage[NBATCH * SV];
-  __shared__ uint16_t s_list[NW][NBATCH];
-  __shared__ uint32_t s_nfrag;
+  __shared__ FwdLds<TW, TH, NBATCH> L;
+  __shared__ float s_alpha[NW][KMAX][64];   // alphas of the core, by slot and lane
 
   const ViewParams &V = vs.v[ti.v];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int bx = (wave % BX) * 8, by = (wave / BX) * 8;
-  const int lx = bx + (lane & 7), ly = by + (lane >> 3);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lx = (wave % BX) * 8 + part_x(lane), ly = (wave / BX) * 8 + part_y(lane);
   const int px0 = ti.tx * TW, py0 = ti.ty * TH;
   const int px = px0 + lx, py = py0 + ly;
   const bool inside = (px < V.width) && (py < V.height);
   // a failed front end (overflow) leaves every
   // tile empty: background, and no list or record is read
-  const uint2 rg = front_failed(w) ? make_uint2(0u, 0u) : w.ranges[ti.t];
+  uint2 rg = front_failed(w) ? make_uint2(0u, 0u) : w.ranges[ti.t];
+  rg.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.x);
+  rg.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.y);
   PixQ u;
   u.x = (float)lx - 0.5f * (float)(TW - 1);
   u.y = (float)ly - 0.5f * (float)(TH - 1);
   u.xx = u.x * u.x; u.xy = u.x * u.y; u.yy = u.y * u.y;   // exact (half-integers)
-  const int cx2 = 2 * px0 + TW - 1, cy2 = 2 * py0 + TH - 1;
   const int K = EXACT ? KMAX : cfg.K;
-  const float tau_core = cfg.tau_core, amax = cfg.alpha_max;
-  const bool no_tail = cfg.no_tail != 0;
+  // (K = 0: no alpha reaches the core)
+  const float tau_core = K > 0 ? cfg.tau_core : 2.f, amax = cfg.alpha_max;
+  const int no_tail = cfg.no_tail;
   const float *recs = w.records + (int64_t)ti.v * cfg.n * kRecFloats;
-  const uint64_t lanemask_lt = (1ull << lane) - 1ull;
 
-  // Core: depth, list position and (CARRY) alpha of up to K fragments,
-  // sorted by depth (ties keep list order). Every fragment is added to the
-  // running sums (alpha, alpha rgb, prod 1 - alpha); once the list is done
-  // the core members are taken back out of them with the same alphas, which
-  // leaves exactly the tail sums. Cores of up to 8 entries carry the alphas
-  // through the insertion; larger ones recompute them from the records at
-  // the end (same staging and arithmetic, so the same values), which keeps
-  // 16 registers free for occupancy.
-  constexpr bool CARRY = KMAX <= 8;
-  float cz[KMAX], ca[KMAX];
-  int cp[KMAX];
+  // Core: the KMAX front-most fragments with alpha >= tau_K, sorted by
+  // (depth, list position); with K < KMAX the first K are used. An entry's
+  // alpha lies in LDS, in the slot its key names; a new entry takes the slot
+  // of the one that drops out. Every fragment is added to the running sums
+  // (alpha, alpha rgb, prod 1 - alpha); once the list is done the core
+  // members are taken back out of them with the same alphas, which leaves
+  // exactly the tail sums. Keys as doubles take 15 instructions per
+  // insertion for K = 8; depth, position and alpha shifted by compares and
+  // selects took 48.
+  constexpr int SB = log2_of(KMAX);   // slot bits; list positions are below 2^27
+  double key[KMAX];
 #pragma unroll
-  for (int i = 0; i < KMAX; ++i) {
-    cz[i] = INFINITY; ca[i] = 0.f; cp[i] = -1;
-  }
-  float zlast = INFINITY;
+  for (int i = 0; i < KMAX; ++i) key[i] = core_key(0x7f800000u, (uint32_t)i);
   float A = 0.f, S0 = 0.f, S1 = 0.f, S2 = 0.f, P = 1.f;
   uint32_t nfrag = 0;
-  if (tid == 0) s_nfrag = 0u;
+  float *my_alpha = &s_alpha[wave][0][lane];
+  if (tid < F_FLOATS / 4) L.stage[NBATCH * (F_FLOATS / 4) + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
 
   for (uint32_t base = rg.x; base < rg.y; base += NBATCH) {
     const int cnt = (int)min((uint32_t)NBATCH, rg.y - base);
     __syncthreads();
-#pragma unroll
-    for (int r0 = 0; r0 < NBATCH; r0 += NT) {
-      const int r = r0 + tid;
-      if (r < cnt) {
-        const uint32_t gid = vals[base + r];
-        float rec[kRecFloats];
-        load_record(recs, gid, rec);
-        float st[F_FLOATS];
-        stage_fwd(rec, cx2, cy2, st);
-        const uint32_t b0 = __float_as_uint(rec[R_BB0]), b1 = __float_as_uint(rec[R_BB1]);
-        st[F_BB + 0] = __int_as_float((int)(b0 & 0xffffu) - px0);
-        st[F_BB + 1] = __int_as_float((int)(b0 >> 16) - py0);
-        st[F_BB + 2] = __int_as_float((int)(b1 & 0xffffu) - px0);
-        st[F_BB + 3] = __int_as_float((int)(b1 >> 16) - py0);
-#pragma unroll
-        for (int k = 0; k < SV; ++k)
-          s_stage[r * SV + k] = make_float4(st[4 * k], st[4 * k + 1], st[4 * k + 2], st[4 * k + 3]);
-      }
-    }
-    __syncthreads();
-    // This wave's list: the staged splats whose pixel rect meets its block.
-    int nlist = cnt;
-    if constexpr (NW > 1) {
-      nlist = 0;
-      for (int j0 = 0; j0 < cnt; j0 += 64) {
-        const int j = j0 + lane;
-        bool hit = false;
-        if (j < cnt) {
-          const float4 b = s_stage[j * SV + F_BB / 4];
-          const float bb[4] = {b.x, b.y, b.z, b.w};
-          hit = rect_meets_block(bb, bx, by);
-        }
-        const uint64_t mk = __ballot(hit);
-        if (hit) s_list[wave][nlist + __popcll(mk & lanemask_lt)] = (uint16_t)j;
-        nlist += __popcll(mk);
-      }
-      __builtin_amdgcn_wave_barrier();
-    }
+    const int nlist = stage_batch(L, recs, vals + base, cnt, px0, py0, wave, lane);
     if (!inside) continue;
-    auto stage_index = [&](int q) -> int {
-      if constexpr (NW > 1) return s_list[wave][q];
-      else return q;
+    const char *rows = reinterpret_cast<const char *>(L.stage);
+    // (opaque: otherwise each component is read by itself where it is used)
+    auto row4 = [&](uint32_t off, int k) -> float4v {
+      float4v t = *reinterpret_cast<const float4v *>(rows + off + 16 * k);
+      asm("" : "+v"(t));
+      return t;
     };
-    auto fetch = [&](int j, float *e) {
+    auto step = [&](uint32_t off) {
+      float e[12];
 #pragma unroll
-      for (int k = 0; k < F_TEST4; ++k) {
-        const float4 t = s_stage[j * SV + k];
+      for (int k = 0; k < 3; ++k) {
+        const float4v t = *reinterpret_cast<const float4v *>(rows + off + 16 * k);
         e[4 * k] = t.x; e[4 * k + 1] = t.y; e[4 * k + 2] = t.z; e[4 * k + 3] = t.w;
       }
-    };
-    auto step = [&](int j, const float *e) {
+      const float4v f3 = row4(off, F_RC / 4);   // rho_c, o, r, g
       const float dd = eval_dd(e + F_QD, u);
       const float mm = eval_mm(e + F_QM, u);
-      if (!is_fragment(dd, mm, e[F_RC])) return;
+      if (!is_fragment(dd, mm, f3.x)) return;
       ++nfrag;
       const float inv = rcp_fast(dd);
-      const float alpha = frag_alpha(e[F_O], mm, inv, amax);
-      const float4 f5 = s_stage[j * SV + F_QZ / 4 + 1];   // qz4, qz5, g, b
-      if (!no_tail) {   // uniform: a kernel argument
+      const float alpha = frag_alpha(f3.y, mm, inv, amax);
+      const float4v f4 = row4(off, F_B / 4);   // b, muz, qz4, qz5
+      int nt = no_tail;
+      asm volatile("" : "+s"(nt));   // (a scalar test here, not a saved lane mask)
+      if (nt == 0) {
         A += alpha;
-        S0 = fmaf(alpha, e[F_R], S0);
-        S1 = fmaf(alpha, f5.z, S1);
-        S2 = fmaf(alpha, f5.w, S2);
+        S0 = fmaf(alpha, f3.z, S0);
+        S1 = fmaf(alpha, f3.w, S1);
+        S2 = fmaf(alpha, f4.x, S2);
         P *= 1.f - alpha;
       }
-      if (alpha >= tau_core && K > 0) {
-        const float4 f4 = s_stage[j * SV + F_QZ / 4];     // qz0..qz3
-        const float qz[6] = {f4.x, f4.y, f4.z, f4.w, f5.x, f5.y};
-        const float z = fmaf(eval_q(qz, u), inv, e[F_MUZ]);
-        if (z < zlast) {
-          // Insert at the first entry deeper than z; the entries from there
-          // on move back by one and the last one drops out of the core. On
-          // the sorted depths that is new[i] = median(old[i-1], old[i], z)
-          // (one instruction); the positions follow the comparisons.
-          const int pos = (int)(base - rg.x) + j;
-          bool c[KMAX];
-#pragma unroll
-          for (int i = 0; i < KMAX; ++i) c[i] = z < cz[i];
-          // (Entries at K and beyond, if K < KMAX, are shifted too but never
-          // read.)
-#pragma unroll
-          for (int i = KMAX - 1; i >= 1; --i) {
-            cp[i] = c[i - 1] ? cp[i - 1] : (c[i] ? pos : cp[i]);
-            if constexpr (CARRY) ca[i] = c[i - 1] ? ca[i - 1] : (c[i] ? alpha : ca[i]);
-            cz[i] = __builtin_amdgcn_fmed3f(cz[i - 1], cz[i], z);
-          }
-          cp[0] = c[0] ? pos : cp[0];
-          if constexpr (CARRY) ca[0] = c[0] ? alpha : ca[0];
-          cz[0] = c[0] ? z : cz[0];
-          if (K == KMAX) {
-            zlast = cz[KMAX - 1];
-          } else {
-#pragma unroll
-            for (int i = 0; i < KMAX; ++i)
-              if (i == K - 1) zlast = cz[i];
-          }
+      if (alpha >= tau_core) {
+        const float4v f5 = row4(off, F_QZ / 4);   // qz0..qz3
+        const float qz[6] = {f5.x, f5.y, f5.z, f5.w, f4.z, f4.w};
+        const float z = fmaf(eval_q(qz, u), inv, f4.y);
+        if (z < __uint_as_float(key_hi(key[KMAX - 1]))) {
+          const uint32_t slot = key_lo(key[KMAX - 1]) & (uint32_t)(KMAX - 1);
+          // row / kStageBytes for whole rows
+          const uint32_t pos = (base - rg.x) + ((off * 683u) >> 16);
+          my_alpha[slot * 64u] = alpha;
+          core_insert<KMAX>(key, core_key(__float_as_uint(z), (pos << SB) | slot));
         }
       }
     };
-    // One staged splat per step, its ray-test values read from LDS just
-    // before use: without a second register buffer for the next splat the
-    // 8x8 forward stays under 96 VGPRs (5 waves per SIMD), and the extra
-    // wave hides the LDS latency better than the buffer did.
-    for (int q = 0; q < nlist; ++q) {
-      const int ja = stage_index(q);
-      float ea[4 * F_TEST4];
-      fetch(ja, ea);
-      step(ja, ea);
+    // Two splats per round; the next round's rows are looked up meanwhile
+    // (the last look-up lies past the list, inside L, and is not used).
+    const uint32_t *list = reinterpret_cast<const uint32_t *>(L.list[wave][lane / kPartLanes]);
+    uint32_t next = list[0];
+    for (int q = 0; q < nlist; q += 2) {
+      const uint32_t o = next;
+      next = list[q / 2 + 1];
+      step(o & 0xffffu);
+      step(o >> 16);
     }
   }
-  __syncthreads();
-  if (nfrag) atomicAdd(&s_nfrag, nfrag);
-  __syncthreads();
-  if (tid == 0 && s_nfrag) count_add(w.frags, (unsigned long long)s_nfrag);
+  static_assert(kStageBytes == 96 && NBATCH <= 256, "row numbers from byte offsets");
+  add_fragments(w, nfrag, lane);
   if (!inside) return;
 
   // Composite (Eq. pixel_color_computation): the core front to back, then
@@ -470,10 +633,11 @@ __device__ __forceinline__ void fwd_tile(const TileInfo &ti, const Ws &w, const 
   uint32_t ncore = 0;
   // tile-major state: this tile's values, value by value, each over the
   // tile's 8x8 blocks (this wave's block is block number `wave`)
-  float *sp = state ? state + tile_state_off(V, ti, state_values(K), NT) + wave * 64 + lane
+  const int blk_pix = part_y(lane) * 8 + part_x(lane);
+  float *sp = state ? state + tile_state_off(V, ti, state_values(K), NT) + wave * 64 + blk_pix
                     : nullptr;
   // One core member: composite, take it out of the sums, store it.
-  auto core_entry = [&](int i, int gid, float a, float r, float g, float b) {
+  auto core_entry = [&](int i, int gid, int pos, float a, float r, float g, float b) {
     if (gid >= 0) {
       const float wgt = a * T;
       C0 = fmaf(wgt, r, C0);
@@ -489,50 +653,37 @@ __device__ __forceinline__ void fwd_tile(const TileInfo &ti, const Ws &w, const 
     if (sp) {
       sp[(int64_t)i * NT] = __int_as_float(gid);
       sp[(int64_t)(K + i) * NT] = a;
-      sp[(int64_t)(2 * K + i) * NT] = __int_as_float(cp[i]);
+      sp[(int64_t)(2 * K + i) * NT] = __int_as_float(pos);
       sp[(int64_t)(3 * K + 3 * i) * NT] = r;
       sp[(int64_t)(3 * K + 3 * i + 1) * NT] = g;
       sp[(int64_t)(3 * K + 3 * i + 2) * NT] = b;
     }
   };
-  if constexpr (CARRY) {
-    // ids, then colours: every entry's loads are independent of the others'
-    int gids[KMAX];
-    float crgb[KMAX][3];
+  // Ids, then colours and alphas, eight entries at a time: the loads of a
+  // group are independent of each other.
+  constexpr int GR = KMAX < 8 ? KMAX : 8;
 #pragma unroll
-    for (int i = 0; i < KMAX; ++i)
-      gids[i] = (i < K && cp[i] >= 0) ? (int)vals[rg.x + (uint32_t)cp[i]] : -1;
+  for (int i0 = 0; i0 < KMAX; i0 += GR) {
+    int gids[GR], pos[GR];
+    float4 c[GR];
+    float ca[GR];
 #pragma unroll
-    for (int i = 0; i < KMAX; ++i) {
-      float4 c = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int i = 0; i < GR; ++i) {
+      const bool got = i0 + i < K && key_hi(key[i0 + i]) != 0x7f800000u;
+      const uint32_t lo = key_lo(key[i0 + i]);
+      pos[i] = got ? (int)(lo >> SB) : -1;
+      gids[i] = got ? (int)vals[rg.x + (lo >> SB)] : -1;
+      ca[i] = got ? my_alpha[(lo & (uint32_t)(KMAX - 1)) * 64u] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < GR; ++i) {
+      c[i] = make_float4(0.f, 0.f, 0.f, 0.f);
       if (gids[i] >= 0)
-        c = reinterpret_cast<const float4 *>(recs + (int64_t)gids[i] * kRecFloats)[R_RGB / 4];
-      crgb[i][0] = c.x; crgb[i][1] = c.y; crgb[i][2] = c.z;
+        c[i] = reinterpret_cast<const float4 *>(recs + (int64_t)gids[i] * kRecFloats)[R_RGB / 4];
     }
 #pragma unroll
-    for (int i = 0; i < KMAX; ++i)
-      if (i < K)
-        core_entry(i, gids[i], gids[i] >= 0 ? ca[i] : 0.f, crgb[i][0], crgb[i][1], crgb[i][2]);
-  } else {
-#pragma unroll
-    for (int i = 0; i < KMAX; ++i) {
-      if (i < K) {
-        int gid = -1;
-        float a = 0.f, r = 0.f, g = 0.f, b = 0.f;
-        if (cp[i] >= 0) {
-          gid = (int)vals[rg.x + (uint32_t)cp[i]];
-          float rec[kRecFloats];
-          load_record(recs, gid, rec);
-          // the same staging and arithmetic as in the list walk: the same alpha
-          float st[F_FLOATS];
-          stage_fwd(rec, cx2, cy2, st);
-          const float dd = eval_dd(st + F_QD, u), mm = eval_mm(st + F_QM, u);
-          a = frag_alpha(st[F_O], mm, rcp_fast(dd), amax);
-          r = st[F_R]; g = st[F_G]; b = st[F_B];
-        }
-        core_entry(i, gid, a, r, g, b);
-      }
-    }
+    for (int i = 0; i < GR; ++i)
+      if (i0 + i < K) core_entry(i0 + i, gids[i], pos[i], ca[i], c[i].x, c[i].y, c[i].z);
   }
   // Tail sums: everything minus the core; exactly empty when no fragment
   // is left over, or when the tail is left out (inference without the
@@ -584,80 +735,45 @@ __device__ __forceinline__ void fwd_tile_sorted(const TileInfo &ti, const Ws &w,
                                                 float *__restrict__ state,
                                                 const uint32_t *__restrict__ vals) {
   constexpr int NT = TW * TH;
-  constexpr int NW = NT / 64;
   constexpr int BX = TW / 8;
-  constexpr int SV = F_FLOATS / 4;
-  __shared__ float4 s_stage[NT * SV];
-  __shared__ uint16_t s_list[NW][NT];
-  __shared__ uint32_t s_nfrag;
+  __shared__ FwdLds<TW, TH, NT> L;
 
   const ViewParams &V = vs.v[ti.v];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int bx = (wave % BX) * 8, by = (wave / BX) * 8;
-  const int lx = bx + (lane & 7), ly = by + (lane >> 3);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lx = (wave % BX) * 8 + part_x(lane), ly = (wave / BX) * 8 + part_y(lane);
   const int px0 = ti.tx * TW, py0 = ti.ty * TH;
   const int px = px0 + lx, py = py0 + ly;
   const bool inside = (px < V.width) && (py < V.height);
-  const uint2 rg = front_failed(w) ? make_uint2(0u, 0u) : w.ranges[ti.t];
+  uint2 rg = front_failed(w) ? make_uint2(0u, 0u) : w.ranges[ti.t];
+  rg.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.x);
+  rg.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.y);
   PixQ u;
   u.x = (float)lx - 0.5f * (float)(TW - 1);
   u.y = (float)ly - 0.5f * (float)(TH - 1);
   u.xx = u.x * u.x; u.xy = u.x * u.y; u.yy = u.y * u.y;
-  const int cx2 = 2 * px0 + TW - 1, cy2 = 2 * py0 + TH - 1;
   const float amax = cfg.alpha_max, tau_T = cfg.tau_T;
   const float *recs = w.records + (int64_t)ti.v * cfg.n * kRecFloats;
-  const uint64_t lanemask_lt = (1ull << lane) - 1ull;
 
   float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
   bool done = !inside;
   int nb = 0, end_pos = 0, stop_pos = -1;
-  if (tid == 0) s_nfrag = 0u;
+  if (tid < F_FLOATS / 4) L.stage[NT * (F_FLOATS / 4) + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
 
   for (uint32_t base = rg.x; base < rg.y; base += NT) {
     // (also the barrier before the stage is overwritten)
     if (__syncthreads_and(done)) break;
     const int cnt = (int)min((uint32_t)NT, rg.y - base);
-    if (tid < cnt) {
-      const uint32_t gid = vals[base + tid];
-      float rec[kRecFloats];
-      load_record(recs, gid, rec);
-      float st[F_FLOATS];
-      stage_fwd(rec, cx2, cy2, st);
-      const uint32_t b0 = __float_as_uint(rec[R_BB0]), b1 = __float_as_uint(rec[R_BB1]);
-      st[F_BB + 0] = __int_as_float((int)(b0 & 0xffffu) - px0);
-      st[F_BB + 1] = __int_as_float((int)(b0 >> 16) - py0);
-      st[F_BB + 2] = __int_as_float((int)(b1 & 0xffffu) - px0);
-      st[F_BB + 3] = __int_as_float((int)(b1 >> 16) - py0);
-#pragma unroll
-      for (int k = 0; k < SV; ++k)
-        s_stage[tid * SV + k] = make_float4(st[4 * k], st[4 * k + 1], st[4 * k + 2], st[4 * k + 3]);
-    }
-    __syncthreads();
-    int nlist = cnt;
-    if constexpr (NW > 1) {
-      nlist = 0;
-      for (int j0 = 0; j0 < cnt; j0 += 64) {
-        const int j = j0 + lane;
-        bool hit = false;
-        if (j < cnt) {
-          const float4 b = s_stage[j * SV + F_BB / 4];
-          const float bb[4] = {b.x, b.y, b.z, b.w};
-          hit = rect_meets_block(bb, bx, by);
-        }
-        const uint64_t mk = __ballot(hit);
-        if (hit) s_list[wave][nlist + __popcll(mk & lanemask_lt)] = (uint16_t)j;
-        nlist += __popcll(mk);
-      }
-      __builtin_amdgcn_wave_barrier();
-    }
+    const int nlist = stage_batch(L, recs, vals + base, cnt, px0, py0, wave, lane);
     if (done) continue;
+    const char *rows = reinterpret_cast<const char *>(L.stage);
+    const uint16_t *list = L.list[wave][lane / kPartLanes];
     for (int q = 0; q < nlist; ++q) {
-      int j = q;
-      if constexpr (NW > 1) j = s_list[wave][q];
+      const uint32_t off = list[q];
       float e[4 * F_TEST4];
 #pragma unroll
       for (int k = 0; k < F_TEST4; ++k) {
-        const float4 t = s_stage[j * SV + k];
+        const float4 t = *reinterpret_cast<const float4 *>(rows + off + 16 * k);
         e[4 * k] = t.x; e[4 * k + 1] = t.y; e[4 * k + 2] = t.z; e[4 * k + 3] = t.w;
       }
       const float dd = eval_dd(e + F_QD, u);
@@ -665,26 +781,23 @@ __device__ __forceinline__ void fwd_tile_sorted(const TileInfo &ti, const Ws &w,
       if (!is_fragment(dd, mm, e[F_RC])) continue;
       const float alpha = frag_alpha(e[F_O], mm, rcp_fast(dd), amax);
       const float tn = T * (1.f - alpha);
-      const int pos = (int)(base - rg.x) + j;
+      const int pos = (int)((base - rg.x) + ((off * 683u) >> 16));
       if (tn < tau_T) {
         done = true;
         stop_pos = pos;
         break;
       }
-      const float4 f5 = s_stage[j * SV + F_QZ / 4 + 1];   // qz4, qz5, g, b
+      const float bl = *reinterpret_cast<const float *>(rows + off + 4 * F_B);
       const float wgt = alpha * T;
       C0 = fmaf(wgt, e[F_R], C0);
-      C1 = fmaf(wgt, f5.z, C1);
-      C2 = fmaf(wgt, f5.w, C2);
+      C1 = fmaf(wgt, e[F_G], C1);
+      C2 = fmaf(wgt, bl, C2);
       T = tn;
       ++nb;
       end_pos = pos + 1;
     }
   }
-  __syncthreads();
-  if (nb) atomicAdd(&s_nfrag, (uint32_t)nb);
-  __syncthreads();
-  if (tid == 0 && s_nfrag) count_add(w.frags, (unsigned long long)s_nfrag);
+  add_fragments(w, (uint32_t)nb, lane);
   if (!inside) return;
   const int64_t npix = (int64_t)V.width * V.height;
   const int64_t pix = (int64_t)py * V.width + px;
@@ -692,7 +805,8 @@ __device__ __forceinline__ void fwd_tile_sorted(const TileInfo &ti, const Ws &w,
   V.out_rgb[npix + pix] = fmaf(T, cfg.bg[1], C1);
   V.out_rgb[2 * npix + pix] = fmaf(T, cfg.bg[2], C2);
   if (state) {
-    float *sp = state + tile_state_off(V, ti, kSortedStateValues, NT) + wave * 64 + lane;
+    float *sp = state + tile_state_off(V, ti, kSortedStateValues, NT) + wave * 64 +
+                part_y(lane) * 8 + part_x(lane);
     sp[0] = T;
     sp[NT] = C0;
     sp[2 * NT] = C1;
@@ -1134,23 +1248,15 @@ __device__ __forceinline__ void bwd_tile(const TileInfo &ti, const Ws &w, const 
 }
 
 // Minimum waves per SIMD asked of the compiler for the forward (HIP's
-// second launch bound): 4 keeps up to 128 VGPRs per lane, which the
-// forward with a core of up to 8 entries fits in without spilling (8x8
-// tiles stay under 96, 5 waves). The macros let a build try other bounds.
-#ifndef HTGS_FWD_WAVES_NARROW
-#define HTGS_FWD_WAVES_NARROW 4
-#endif
-#ifndef HTGS_FWD_WAVES_WIDE
-#define HTGS_FWD_WAVES_WIDE 4
-#endif
-template <int KMAX, int TW, int BM>
+// second launch bound): what LDS leaves room for (8x8 tiles with K = 8 take
+// 8.8 KiB per wave, 18 waves per CU).
+template <int KMAX, int TW, int TH, int BM>
 constexpr int fwd_simd_waves() {
-  // (a doubled LDS batch holds the forward at 3 workgroups per SIMD anyway)
-  return (KMAX > 8 || BM > 1) ? 1 : (TW == 8 ? HTGS_FWD_WAVES_NARROW : HTGS_FWD_WAVES_WIDE);
+  return (KMAX > 8 || BM > 1 || TW * TH > 128) ? 1 : 4;
 }
 
 template <int KMAX, int TW, int TH, int BM, bool EXACT, bool PERSIST>
-__global__ void __launch_bounds__((TW * TH), (fwd_simd_waves<KMAX, TW, BM>()))
+__global__ void __launch_bounds__((TW * TH), (fwd_simd_waves<KMAX, TW, TH, BM>()))
     k_raster_fwd(Ws w, ViewSet vs, KCfg cfg, float *__restrict__ state,
                  const uint32_t *__restrict__ vals) {
 #define HTGS_FWD_BODY(T) fwd_tile<KMAX, TW, TH, BM, EXACT>(T, w, vs, cfg, state, vals)
