@@ -126,10 +126,10 @@ typedef struct htgs_camera {
  *             gradients are the same as without it; the tile lists are then
  *             a subset of Sec. 3.2's box lists (forward and backward of one
  *             frame must use the same flag);
- *             HTGS_FLAG_PERSISTENT: the raster launches hold as many
- *             workgroups as fit on the device at once, each pulling tiles
- *             from an atomic queue (in descending-cost order with
- *             HTGS_FLAG_COST_ORDER) until it runs out;
+ *             HTGS_FLAG_PERSISTENT: accepted and without effect. The
+ *             hardware hands the tiles (in descending-cost order with
+ *             HTGS_FLAG_COST_ORDER) to the workgroups as they finish, which
+ *             is the queue that this flag once asked for in software;
  *             HTGS_FLAG_NO_TAIL: inference without the tail (Sec. 4.3,
  *             "Hybrid Transparency Ablations"): C = sum over the core of
  *             alpha_i T_i c_i + T_{n+1} c_bg, every non-core fragment left

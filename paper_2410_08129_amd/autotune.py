@@ -21,7 +21,7 @@ from . import htgs
 
 CANDIDATES = (
     # (tile width, tile height, lds_batch multiplier, cost order, tile culling,
-    #  persistent tile queue)
+    #  tile queue: without effect, its names stay known)
     (8, 8, 1, False, False, False), (8, 8, 2, False, False, False),
     (8, 8, 1, True, False, False), (8, 8, 2, True, False, False),
     (16, 8, 1, False, False, False), (16, 16, 1, False, False, False),

@@ -261,7 +261,16 @@ ViewSet make_views(const htgs_camera *cams, int32_t n_views, const htgs_config *
   return vs;
 }
 
-KCfg make_kcfg(const htgs_gaussians *g, const htgs_config *cfg) {
+// Tile slots an XCD takes in a row (xcd_slot): at most 1 << kMaxXcdShift,
+// and at least kMinXcdChunks such chunks in a frame, so that every XCD gets
+// several from all over it. The launches depend little on the size: at
+// 1080p without the cost order 1.536, 1.534, 1.530 and 1.532 ms per step for
+// 1, 8, 32 and 128 tiles, with it 1.473, 1.459, 1.463 and 1.472; one band of
+// the frame per XCD (the most crowded band sets the time) took 1.740.
+constexpr int kMaxXcdShift = 3;
+constexpr int64_t kMinXcdChunks = 64;
+
+KCfg make_kcfg(const htgs_gaussians *g, const htgs_config *cfg, int64_t tiles) {
   KCfg k;
   k.n = g->n;
   k.K = cfg->K;
@@ -276,7 +285,8 @@ KCfg make_kcfg(const htgs_gaussians *g, const htgs_config *cfg) {
   k.cost_order = (cfg->flags & HTGS_FLAG_COST_ORDER) ? 1 : 0;
   k.grad_overwrite = (cfg->flags & HTGS_FLAG_GRAD_OVERWRITE) ? 1 : 0;
   k.tile_cull = (cfg->flags & HTGS_FLAG_TILE_CULL) ? 1 : 0;
-  k.persistent = (cfg->flags & HTGS_FLAG_PERSISTENT) ? 1 : 0;
+  k.xcd_shift = 0;
+  while (k.xcd_shift < kMaxXcdShift && (tiles >> (k.xcd_shift + 1)) >= kMinXcdChunks) ++k.xcd_shift;
   k.no_tail = (cfg->flags & HTGS_FLAG_NO_TAIL) ? 1 : 0;
   k.baked = (cfg->flags & HTGS_FLAG_BAKED) ? 1 : 0;
   k.sorted = sorted_of(cfg) ? 1 : 0;
@@ -359,7 +369,7 @@ int run_front(const htgs_gaussians *g, const ViewSet &vs, const htgs_config *cfg
   }
   {
     StageTimer t(HTGS_STAGE_PREPROCESS, s, 1, timed);
-    HIP_TRY(launch_preprocess(make_gp(g), make_kcfg(g, cfg), vs, w, s));
+    HIP_TRY(launch_preprocess(make_gp(g), make_kcfg(g, cfg, vs.total_tiles), vs, w, s));
   }
   if (sort && L.capacity > 0) {
     StageTimer t(HTGS_STAGE_SORT, s, 3 * L.passes, timed);
@@ -393,9 +403,7 @@ int forward_impl(const htgs_gaussians *g, const htgs_camera *cams, int32_t n_vie
   if ((e = run_front(g, vs, cfg, L, ws, s, true, partials))) return e;
   const Ws w = make_ws(ws, L);
   StageTimer t(HTGS_STAGE_RASTER_FWD, s, 1, partials);
-  if (cfg->flags & HTGS_FLAG_PERSISTENT)
-    HIP_TRY(launch_fill_zero(static_cast<char *>(ws) + L.status + 4 * kQueueFwd, 16, s));
-  HIP_TRY(launch_raster_fwd(w, vs, make_kcfg(g, cfg), static_cast<float *>(state),
+  HIP_TRY(launch_raster_fwd(w, vs, make_kcfg(g, cfg, tiles), static_cast<float *>(state),
                             w.vals[w.final_buf], s));
   return HTGS_OK;
 }
@@ -422,12 +430,10 @@ int backward_impl(const htgs_gaussians *g, const htgs_camera *cams, int32_t n_vi
   const Layout L = make_layout(g->n, n_views, tiles, cap, true, sorted_of(cfg));
   const ViewSet vs = make_views(cams, n_views, cfg, nullptr, grad_rgb);
   const Ws w = make_ws(ws, L);
-  const KCfg k = make_kcfg(g, cfg);
+  const KCfg k = make_kcfg(g, cfg, tiles);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (cap > 0) {
     StageTimer t(HTGS_STAGE_RASTER_BWD, s);
-    if (cfg->flags & HTGS_FLAG_PERSISTENT)
-      HIP_TRY(launch_fill_zero(static_cast<char *>(ws) + L.status + 4 * kQueueBwd, 16, s));
     HIP_TRY(launch_raster_bwd(w, vs, k, static_cast<const float *>(state), w.vals[w.final_buf], s));
   }
   // The preprocess backward sums the instance partials per (Gaussian, view)

@@ -75,7 +75,7 @@ struct KCfg {
   int32_t cost_order;   // raster workgroups take tiles in descending-cost order
   int32_t grad_overwrite;  // preprocess backward stores gradients instead of adding
   int32_t tile_cull;       // drop rect tiles that no fragment can reach (rects of <= 64 tiles)
-  int32_t persistent;      // raster workgroups pull tiles from an atomic queue
+  int32_t xcd_shift;       // log2 of the tile slots an XCD takes in a row (xcd_slot)
   int32_t no_tail;         // forward leaves the tail out (inference)
   int32_t baked;           // inputs hold scales, unit quaternions and opacities
   int32_t sorted;          // alpha blending in mean-depth order with an early stop
@@ -97,7 +97,7 @@ constexpr uint32_t kCflagVisible = 8u;
 
 // Device addresses inside the caller's workspace.
 struct Ws {
-  uint32_t *status;            // [kStatusWords]: flags, raster queues (see below)
+  uint32_t *status;            // [kStatusWords]: flags (see below)
   unsigned long long *total;   // instance count (64-bit)
   unsigned long long *frags;   // fragments counted by the forward raster (spread, below)
   unsigned long long *frags_bwd;  // fragments counted by the backward raster (spread)
@@ -205,19 +205,14 @@ __device__ __forceinline__ void count_add(unsigned long long *ctr, unsigned long
 // workgroup of any launch waits for another, so nothing else can fail).
 enum StatusBits : uint32_t { ST_OVERFLOW = 1u };
 constexpr uint32_t kStatusPublic = ST_OVERFLOW;
-// Status words (512 bytes, four 128-byte cache lines). The flags word has a
-// line of its own: every workgroup of the later stages reads it. [0] flags;
-// [64..67] / [68..71] the raster queues.
+// Status words (512 bytes): [0] the flags, alone in their 128-byte cache
+// line, which every workgroup of the later stages reads.
 constexpr int kStatusWords = 128;
 // outputs of the front end are unusable: overflow
 __device__ __forceinline__ bool front_failed(const Ws &w) {
   return (__hip_atomic_load(&w.status[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &
           ST_OVERFLOW) != 0u;
 }
-// status words of the persistent raster queues (16-byte aligned, cleared
-// before each raster launch)
-constexpr int kQueueFwd = 64, kQueueBwd = 68;
-
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
 // Instances of one (view, Gaussian): the rect's tiles, or the surviving
@@ -246,12 +241,14 @@ __device__ __forceinline__ uint32_t tslot_slot(uint4 d, int tx, int ty) {
   return d.x + tile_rank((ty - y0) * wdt + (tx - x0), tslot_mask(d));
 }
 
-// Tile coverage rule shared by the forward and backward launchers: tile ids
-// are handed out so that consecutive workgroups on one XCD (workgroups are
-// dealt round-robin over the 8 XCDs) work on a contiguous band of tiles.
-__device__ __forceinline__ int xcd_tile(int block, int total_tiles) {
-  const int per = (total_tiles + 7) >> 3;
-  return (block & 7) * per + (block >> 3);
+// Tile slot of a raster workgroup. Workgroups are dealt round-robin over the
+// 8 XCDs; each XCD takes the slots in chunks of 1 << shift, the XCDs' chunks
+// in turn: neighbouring tiles share most of their splats, whose records then
+// lie in that XCD's L2, while every part of the frame (or of the cost order)
+// is spread over all XCDs.
+__host__ __device__ __forceinline__ int xcd_slot(int block, int shift) {
+  const int i = block >> 3;
+  return ((((i >> shift) << 3) + (block & 7)) << shift) + (i & ((1 << shift) - 1));
 }
 
 __device__ __forceinline__ int view_of_tile(const ViewSet &vs, int t) {

@@ -222,58 +222,22 @@ __device__ __forceinline__ int64_t tile_state_off(const ViewParams &V, const Til
   return V.state_off + ((int64_t)ti.ty * V.tiles_x + ti.tx) * nval * nt;
 }
 
+// The workgroup's tile; false past the last one. (The hardware hands the next
+// workgroup to the first CU with room. Resident workgroups that took tiles
+// from an atomic counter instead waited for it, 13 ns per tile however many
+// asked: 582 against 425 us for the 1080p forward's 32,400 tiles, 996 against
+// 734 us for the 70,752 of an 8-view batch.)
 __device__ __forceinline__ bool tile_info(const ViewSet &vs, const KCfg &cfg, const Ws &w,
                                           TileInfo &ti) {
-  if (cfg.cost_order) {
-    if ((int)blockIdx.x >= vs.total_tiles) return false;
-    ti.t = (int)w.order[blockIdx.x];
-  } else {
-    ti.t = xcd_tile(blockIdx.x, vs.total_tiles);
-    if (ti.t >= vs.total_tiles) return false;
-  }
+  const int slot = xcd_slot((int)blockIdx.x, cfg.xcd_shift);
+  if (slot >= vs.total_tiles) return false;
+  ti.t = cfg.cost_order ? (int)w.order[slot] : slot;
   ti.v = view_of_tile(vs, ti.t);
   const int lt = ti.t - vs.v[ti.v].tile_base;
   ti.tx = lt % vs.v[ti.v].tiles_x;
   ti.ty = lt / vs.v[ti.v].tiles_x;
   return true;
 }
-
-// Tile of queue slot q in persistent mode: descending-cost order when the
-// cost order is on, else row-major.
-__device__ __forceinline__ void tile_of_slot(const ViewSet &vs, const KCfg &cfg, const Ws &w, int q,
-                                             TileInfo &ti) {
-  ti.t = cfg.cost_order ? (int)w.order[q] : q;
-  ti.v = view_of_tile(vs, ti.t);
-  const int lt = ti.t - vs.v[ti.v].tile_base;
-  ti.tx = lt % vs.v[ti.v].tiles_x;
-  ti.ty = lt / vs.v[ti.v].tiles_x;
-}
-
-// Runs BODY(ti) for the workgroup's tile, or, in persistent mode, for tiles
-// taken from the atomic queue w.status[QSLOT] until it is exhausted (every
-// workgroup leaves when the queue passes the tile count). PERSIST is a
-// compile-time choice: the queue loop and its LDS word would otherwise cost
-// the one-tile kernels registers and, for 8x8 backward tiles, a workgroup
-// per CU (16 KiB of LDS plus that word).
-#define HTGS_FOR_TILES(PERSIST, QSLOT, BODY)                                     \
-  do {                                                                           \
-    if constexpr (!(PERSIST)) {                                                  \
-      TileInfo ti_;                                                              \
-      if (tile_info(vs, cfg, w, ti_)) BODY(ti_);                                 \
-    } else {                                                                     \
-      __shared__ int s_next_;                                                    \
-      for (;;) {                                                                 \
-        __syncthreads();                                                         \
-        if (threadIdx.x == 0) s_next_ = (int)atomicAdd(&w.status[QSLOT], 1u);    \
-        __syncthreads();                                                         \
-        const int q_ = s_next_;                                                  \
-        if (q_ >= vs.total_tiles) break;                                         \
-        TileInfo ti_;                                                            \
-        tile_of_slot(vs, cfg, w, q_, ti_);                                       \
-        BODY(ti_);                                                               \
-      }                                                                          \
-    }                                                                            \
-  } while (0)
 
 __device__ __forceinline__ bool rect_meets_block(const float *bb, int bx, int by) {
   return (__float_as_int(bb[2]) >= bx) && (__float_as_int(bb[0]) <= bx + 7) &&
@@ -817,13 +781,12 @@ __device__ __forceinline__ void fwd_tile_sorted(const TileInfo &ti, const Ws &w,
   }
 }
 
-template <int TW, int TH, bool PERSIST>
+template <int TW, int TH>
 __global__ void __launch_bounds__(TW * TH)
     k_raster_fwd_sorted(Ws w, ViewSet vs, KCfg cfg, float *__restrict__ state,
                         const uint32_t *__restrict__ vals) {
-#define HTGS_FWDS_BODY(T) fwd_tile_sorted<TW, TH>(T, w, vs, cfg, state, vals)
-  HTGS_FOR_TILES(PERSIST, kQueueFwd, HTGS_FWDS_BODY);
-#undef HTGS_FWDS_BODY
+  TileInfo ti;
+  if (tile_info(vs, cfg, w, ti)) fwd_tile_sorted<TW, TH>(ti, w, vs, cfg, state, vals);
 }
 
 // ---------------------------------------------------------------------------
@@ -1255,25 +1218,23 @@ constexpr int fwd_simd_waves() {
   return (KMAX > 8 || BM > 1 || TW * TH > 128) ? 1 : 4;
 }
 
-template <int KMAX, int TW, int TH, int BM, bool EXACT, bool PERSIST>
+template <int KMAX, int TW, int TH, int BM, bool EXACT>
 __global__ void __launch_bounds__((TW * TH), (fwd_simd_waves<KMAX, TW, TH, BM>()))
     k_raster_fwd(Ws w, ViewSet vs, KCfg cfg, float *__restrict__ state,
                  const uint32_t *__restrict__ vals) {
-#define HTGS_FWD_BODY(T) fwd_tile<KMAX, TW, TH, BM, EXACT>(T, w, vs, cfg, state, vals)
-  HTGS_FOR_TILES(PERSIST, kQueueFwd, HTGS_FWD_BODY);
-#undef HTGS_FWD_BODY
+  TileInfo ti;
+  if (tile_info(vs, cfg, w, ti)) fwd_tile<KMAX, TW, TH, BM, EXACT>(ti, w, vs, cfg, state, vals);
 }
 
-template <int KMAX, int TW, int TH, bool EXACT, bool PERSIST>
+template <int KMAX, int TW, int TH, bool EXACT>
 __global__ void __launch_bounds__((64 * bwd_waves<TW, TH>()), (bwd_simd_waves<KMAX, TW>()))
     k_raster_bwd(Ws w, ViewSet vs, KCfg cfg, const float *__restrict__ state,
                  const uint32_t *__restrict__ vals) {
   // the forward of a failed front end rendered empty tiles: nothing to do
   if (front_failed(w)) return;
   uint32_t nfr = 0;   // fragments this thread differentiated
-#define HTGS_BWD_BODY(T) bwd_tile<KMAX, TW, TH, EXACT>(T, w, vs, cfg, state, vals, nfr)
-  HTGS_FOR_TILES(PERSIST, kQueueBwd, HTGS_BWD_BODY);
-#undef HTGS_BWD_BODY
+  TileInfo ti;
+  if (tile_info(vs, cfg, w, ti)) bwd_tile<KMAX, TW, TH, EXACT>(ti, w, vs, cfg, state, vals, nfr);
   // one atomic per wave (a word of LDS would take the 8x8 and 16x8 kernels
   // past 16 and 32 KiB, one workgroup per CU fewer)
 #pragma unroll
@@ -1527,15 +1488,14 @@ __device__ __forceinline__ void bwd_tile_sorted(const TileInfo &ti, const Ws &w,
   }
 }
 
-template <int TW, int TH, bool PERSIST>
+template <int TW, int TH>
 __global__ void __launch_bounds__(TW * TH)
     k_raster_bwd_sorted(Ws w, ViewSet vs, KCfg cfg, const float *__restrict__ state,
                         const uint32_t *__restrict__ vals) {
   if (front_failed(w)) return;
   uint32_t nfr = 0;
-#define HTGS_BWDS_BODY(T) bwd_tile_sorted<TW, TH>(T, w, vs, cfg, state, vals, nfr)
-  HTGS_FOR_TILES(PERSIST, kQueueBwd, HTGS_BWDS_BODY);
-#undef HTGS_BWDS_BODY
+  TileInfo ti;
+  if (tile_info(vs, cfg, w, ti)) bwd_tile_sorted<TW, TH>(ti, w, vs, cfg, state, vals, nfr);
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) nfr += (uint32_t)__shfl_xor((int)nfr, off, 64);
   if ((threadIdx.x & 63) == 0 && nfr) count_add(w.frags_bwd, (unsigned long long)nfr);
@@ -1544,34 +1504,16 @@ __global__ void __launch_bounds__(TW * TH)
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
-// Workgroups of a persistent launch: as many as can be resident at once.
-static int resident_blocks(const void *kernel, int threads, int tiles) {
-  static int cus = 0;
-  if (cus == 0) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-      cus = 256;
-  }
-  int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess ||
-      per_cu < 1)
-    per_cu = 1;
-  const int n = per_cu * cus;
-  return n < tiles ? n : (tiles > 0 ? tiles : 1);
+// Workgroups of a raster launch: one per tile slot, the slots in whole groups
+// of eight XCD chunks.
+static dim3 tile_grid(const ViewSet &vs, const KCfg &cfg) {
+  const int group = 8 << cfg.xcd_shift;
+  return dim3((unsigned)((vs.total_tiles + group - 1) / group * group));
 }
 template <int KMAX, int TW, int TH, int BM, bool EXACT>
 static hipError_t fwd_launch_bm(const Ws &w, const ViewSet &vs, const KCfg &cfg, float *state,
                                 const uint32_t *vals, hipStream_t s) {
-  if (cfg.persistent) {
-    auto *kern = k_raster_fwd<KMAX, TW, TH, BM, EXACT, true>;
-    const int blocks = resident_blocks((const void *)kern, TW * TH, vs.total_tiles);
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(TW * TH), 0, s, w, vs, cfg, state, vals);
-  } else {
-    auto *kern = k_raster_fwd<KMAX, TW, TH, BM, EXACT, false>;
-    const int blocks = 8 * ((vs.total_tiles + 7) / 8);
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(TW * TH), 0, s, w, vs, cfg, state, vals);
-  }
+  hipLaunchKernelGGL((k_raster_fwd<KMAX, TW, TH, BM, EXACT>), tile_grid(vs, cfg), dim3(TW * TH), 0, s, w, vs, cfg, state, vals);
   return hipGetLastError();
 }
 
@@ -1588,15 +1530,7 @@ template <int KMAX, int TW, int TH, bool EXACT>
 static hipError_t bwd_launch(const Ws &w, const ViewSet &vs, const KCfg &cfg, const float *state,
                              const uint32_t *vals, hipStream_t s) {
   constexpr int BT = 64 * bwd_waves<TW, TH>();
-  if (cfg.persistent) {
-    auto *kern = k_raster_bwd<KMAX, TW, TH, EXACT, true>;
-    const int blocks = resident_blocks((const void *)kern, BT, vs.total_tiles);
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(BT), 0, s, w, vs, cfg, state, vals);
-  } else {
-    auto *kern = k_raster_bwd<KMAX, TW, TH, EXACT, false>;
-    const int blocks = 8 * ((vs.total_tiles + 7) / 8);
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(BT), 0, s, w, vs, cfg, state, vals);
-  }
+  hipLaunchKernelGGL((k_raster_bwd<KMAX, TW, TH, EXACT>), tile_grid(vs, cfg), dim3(BT), 0, s, w, vs, cfg, state, vals);
   return hipGetLastError();
 }
 
@@ -1654,15 +1588,7 @@ int kmax_for(int K) {
 template <int TW, int TH>
 static hipError_t fwd_sorted_launch(const Ws &w, const ViewSet &vs, const KCfg &cfg, float *state,
                                     const uint32_t *vals, hipStream_t s) {
-  if (cfg.persistent) {
-    auto *kern = k_raster_fwd_sorted<TW, TH, true>;
-    const int blocks = resident_blocks((const void *)kern, TW * TH, vs.total_tiles);
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(TW * TH), 0, s, w, vs, cfg, state, vals);
-  } else {
-    auto *kern = k_raster_fwd_sorted<TW, TH, false>;
-    const int blocks = 8 * ((vs.total_tiles + 7) / 8);
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(TW * TH), 0, s, w, vs, cfg, state, vals);
-  }
+  hipLaunchKernelGGL((k_raster_fwd_sorted<TW, TH>), tile_grid(vs, cfg), dim3(TW * TH), 0, s, w, vs, cfg, state, vals);
   return hipGetLastError();
 }
 
@@ -1680,15 +1606,7 @@ hipError_t launch_raster_fwd(const Ws &w, const ViewSet &vs, const KCfg &cfg, fl
 template <int TW, int TH>
 static hipError_t bwd_sorted_launch(const Ws &w, const ViewSet &vs, const KCfg &cfg,
                                     const float *state, const uint32_t *vals, hipStream_t s) {
-  if (cfg.persistent) {
-    auto *kern = k_raster_bwd_sorted<TW, TH, true>;
-    const int blocks = resident_blocks((const void *)kern, TW * TH, vs.total_tiles);
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(TW * TH), 0, s, w, vs, cfg, state, vals);
-  } else {
-    auto *kern = k_raster_bwd_sorted<TW, TH, false>;
-    const int blocks = 8 * ((vs.total_tiles + 7) / 8);
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(TW * TH), 0, s, w, vs, cfg, state, vals);
-  }
+  hipLaunchKernelGGL((k_raster_bwd_sorted<TW, TH>), tile_grid(vs, cfg), dim3(TW * TH), 0, s, w, vs, cfg, state, vals);
   return hipGetLastError();
 }
 

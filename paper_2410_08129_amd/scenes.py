@@ -96,7 +96,7 @@ class RenderSettings:
     cost_order: bool = False    # rasterize tiles in descending instance-count order
     grad_overwrite: bool = False  # backward writes gradients instead of adding to them
     tile_cull: bool = False     # drop box tiles that the rho_c-ellipse does not reach
-    persistent: bool = False    # raster workgroups pull tiles from an atomic queue
+    persistent: bool = False    # accepted, no effect (the hardware queues the tiles)
     no_tail: bool = False       # inference without the tail (forward only)
     baked: bool = False         # inputs hold scales, unit quaternions and opacities
     sorted_blend: bool = False  # alpha blending in per-tile mean-depth order instead of HT
