@@ -35,11 +35,17 @@
 // atomics, deterministic results.
 #include <float.h>
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace htgs {
 
 typedef float float4v __attribute__((ext_vector_type(4)));   // one 16-byte LDS read
+typedef float float2v __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) const char *lds_bytes;   // a 32-bit LDS address
+typedef __attribute__((address_space(3))) const float2v *lds_float2;
+typedef __attribute__((address_space(3))) const float4v *lds_float4;
 
 constexpr float kNegHalfLog2e = -0.72134752044448170368f;  // -1 / (2 ln 2)
 
@@ -792,25 +798,28 @@ __global__ void __launch_bounds__(TW * TH)
 // ---------------------------------------------------------------------------
 // Backward
 // ---------------------------------------------------------------------------
-// Per-pixel adjoint factors of the hybrid backward in LDS (the core's list
-// positions are read from the forward state when a chunk's core table is
-// built, which keeps the row at 24 floats for K = 8).
+// Per-pixel adjoint factors of the hybrid backward in LDS: G(3), w1, q1, q2,
+// then per fragment code (0: tail, i + 1: core entry i) the pair (dL/dalpha
+// of the core entry, dC/dc per alpha): (unused, w1), (T_i (c_i - B_i) . G,
+// T_i), ... The core's list positions are read from the forward state when a
+// chunk's code table is built.
 template <int KMAX>
 struct PixLayout {
-  // G(3), w1, q1, q2, pad(2), dL/dalpha_i[KMAX], T_i[KMAX]
-  static constexpr int kCoef = 8;
-  static constexpr int kT = 8 + KMAX;
+  static constexpr int kPair = 6;
+  // codes are stored as multiples of this (one byte): offsets of the pairs,
+  // or half of them where 8 K does not fit a byte
+  static constexpr int kCodeUnit = KMAX <= 16 ? 8 : 4;
   static constexpr int kStride = ((8 + 2 * KMAX) + 3) / 4 * 4;
 };
 
-// Gradient contribution of one fragment (lane's splat at pixel Pp, column c
-// of its 8x8 block; c is a constant after unrolling) to the lane's
-// accumulators. cslot is the fragment's core index at this pixel, or -1 for
-// a tail fragment. rs holds this row's sums of the d and m weights times
-// (1, c, c^2).
-template <int KMAX>
-__device__ __forceinline__ void bwd_fragment(float op, const float *rgb, const float *Pp, int c,
-                                             float dd, float mm, int cslot, float amax,
+// Gradient contribution of one fragment (lane's splat at the pixel whose
+// factors lie at Pp, column c of its 8x8 block; c is a constant after
+// unrolling) to the lane's accumulators; code: its fragment code times
+// kCodeUnit. rs holds this row's sums of the d and m weights times (1, c,
+// c^2). CLAMP false: no lane's opacity exceeds the alpha clamp.
+template <int KMAX, bool CLAMP>
+__device__ __forceinline__ void bwd_fragment(float op, const float *rgb, lds_bytes Pp, int c,
+                                             float dd, float mm, uint32_t code, float amax,
                                              float *rs, float *acc) {
   using L = PixLayout<KMAX>;
   // alpha exactly as the forward's frag_alpha forms it
@@ -818,35 +827,29 @@ __device__ __forceinline__ void bwd_fragment(float op, const float *rgb, const f
   const float r2 = mm * inv;
   const float e = exp2_fast(r2 * kNegHalfLog2e);
   const float araw = op * e;
-  const bool unclamped = araw <= amax;
-  const float alpha = unclamped ? araw : amax;
-  const float G0 = Pp[0], G1 = Pp[1], G2 = Pp[2], w1 = Pp[3];
+  float alpha = CLAMP ? __builtin_amdgcn_fmed3f(araw, 0.f, amax) : araw;
+  asm("" : "+v"(alpha));   // (1 - alpha below from the rounded alpha, as the forward's)
+  const float4v gw = *(lds_float4)Pp;            // G, w1
+  const float2v q = *(lds_float2)(Pp + 16);      // q1, q2
+  const float2v core = *(lds_float2)(Pp + (code * (8 / L::kCodeUnit)) + 4 * L::kPair);
   // tail: dC/dalpha = w1 (c - c_tail) - T P (c_bg - c_tail) / (1 - alpha),
   // dC/dc = w1 alpha; core: the pixel's precomputed T_i (c_i - B_i) and T_i
-  const float gdc = fmaf(G2, rgb[2], fmaf(G1, rgb[1], G0 * rgb[0]));
-  const float tail = fmaf(w1, gdc, -Pp[4]) - Pp[5] * rcp_fast(1.f - alpha);
-  // Branch-free: every lane reads a core entry (entry 0 for tail
-  // fragments) and selects.
-  const bool core = cslot >= 0;
-  const int ci = core ? cslot : 0;
-  const float cf = Pp[L::kCoef + ci], cT = Pp[L::kT + ci];
-  const float dLda = core ? cf : tail;
-  const float wc = alpha * (core ? cT : w1);
-  acc[13] = fmaf(wc, G0, acc[13]);
-  acc[14] = fmaf(wc, G1, acc[14]);
-  acc[15] = fmaf(wc, G2, acc[15]);
+  const float gdc = fmaf(gw.z, rgb[2], fmaf(gw.y, rgb[1], gw.x * rgb[0]));
+  const float tail = fmaf(gw.w, gdc, -q.x) - q.y * rcp_fast(1.f - alpha);
+  const float dLda = code ? core.x : tail;
+  const float wc = alpha * core.y;
+  acc[13] = fmaf(wc, gw.x, acc[13]);
+  acc[14] = fmaf(wc, gw.y, acc[14]);
+  acc[15] = fmaf(wc, gw.z, acc[15]);
   // Where alpha is clamped, o and rho^2 receive no gradient.
-  const float g = unclamped ? dLda : 0.f;
+  const float g = !CLAMP || araw <= amax ? dLda : 0.f;
   {
     acc[12] = fmaf(g, e, acc[12]);
     const float s1 = -alpha * g * inv;      // weight of m: 2 dL/drho^2 / |d|^2
     const float s2 = -s1 * r2;              // weight of d
     rs[0] += s2;
     rs[3] += s1;
-    if (c == 1) {
-      rs[1] += s2; rs[2] += s2;
-      rs[4] += s1; rs[5] += s1;
-    } else if (c > 1) {
+    if (c >= 1) {
       const float fc = (float)c, fc2 = (float)(c * c);
       rs[1] = fmaf(fc, s2, rs[1]);
       rs[2] = fmaf(fc2, s2, rs[2]);
@@ -856,12 +859,11 @@ __device__ __forceinline__ void bwd_fragment(float op, const float *rgb, const f
   }
 }
 
-// Writes one instance partial: the lane's moments about the tile's first
-// pixel (acc[0..5] for the d weights, acc[6..11] for the m weights) moved to
+// One instance partial: the lane's moments about the tile's first pixel
+// (acc[0..5] for the d weights, acc[6..11] for the m weights) moved to
 // an origin (a, b) pixels before it (dx = lx + a: sum w dx = S_x + a S,
 // sum w dx^2 = S_xx + 2 a S_x + a^2 S, ...), then dL/do and dL/d(rgb).
-__device__ __forceinline__ void write_partial(const float *acc, float a, float b, float *dstf) {
-  float out[kPartialFloats];
+__device__ __forceinline__ void form_partial(const float *acc, float a, float b, float *out) {
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const float *S = acc + 6 * h;
@@ -877,37 +879,65 @@ __device__ __forceinline__ void write_partial(const float *acc, float a, float b
   out[P_C] = acc[13];
   out[P_C + 1] = acc[14];
   out[P_C + 2] = acc[15];
-  float4 *dst = reinterpret_cast<float4 *>(dstf);
-#pragma unroll
-  for (int k = 0; k < kPartialFloats / 4; ++k)
-    dst[k] = make_float4(out[4 * k], out[4 * k + 1], out[4 * k + 2], out[4 * k + 3]);
 }
 
-// Byte swizzle of the backward's core table rows (see bwd_tile).
-__device__ __forceinline__ constexpr int slot_swz(int q) { return ((q >> 1) & 15) << 2; }
+// The wave's partials to their slots (kNoSlot: none), four lanes per 64-byte
+// partial: a store of the wave then covers 16 partials instead of a quarter
+// of 64, a quarter of the address work (6.6M partials to random slots take
+// 174 instead of 247 us by themselves, the 1080p backward 517 instead of
+// 549 us). buf: 4 KiB of LDS of the wave's own, row r's words rotated by
+// r / 4 (no bank conflicts either way).
+constexpr uint32_t kNoSlot = 0xffffffffu;
+__device__ __forceinline__ void write_partials(const float *acc, float a, float b, uint32_t slot,
+                                               float4 *buf, float *__restrict__ partials, int lane) {
+  float out[kPartialFloats];
+  form_partial(acc, a, b, out);
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    buf[lane * 4 + (k ^ ((lane >> 2) & 3))] =
+        make_float4(out[4 * k], out[4 * k + 1], out[4 * k + 2], out[4 * k + 3]);
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int it = 0; it < 4; ++it) {
+    const int r = it * 16 + (lane >> 2);
+    const uint32_t sl = (uint32_t)__shfl((int)slot, r, 64);
+    const float4 v = buf[r * 4 + ((lane & 3) ^ ((r >> 2) & 3))];
+    if (sl != kNoSlot)
+      reinterpret_cast<float4 *>(partials)[(int64_t)sl * (kPartialFloats / 4) + (lane & 3)] = v;
+  }
+  __builtin_amdgcn_wave_barrier();
+}
 
 // Waves per backward workgroup. A tile's 64-instance chunks are dealt to
 // its waves round-robin, so waves whose share ends early idle until the
-// tile is done: with four waves ~25% of the wave time at 1080p; fewer waves
-// idle less but stage the tile's per-pixel factors for fewer waves.
-#ifndef HTGS_BWD_WAVES_SMALL
-#define HTGS_BWD_WAVES_SMALL 2
-#endif
-#ifndef HTGS_BWD_WAVES_MID
-#define HTGS_BWD_WAVES_MID 4
-#endif
+// tile is done; fewer waves idle less but stage the tile's per-pixel factors
+// for fewer waves. One-block tiles with 1, 2, 3 and 4 waves: 516, 516, 532
+// and 556 us at 1080p (205 instances per tile), 8.78, 7.80, 7.90 and 8.00 ms
+// on the 4K frame (786 per tile).
 template <int TW, int TH>
 constexpr int bwd_waves() {
-  return TW * TH <= 64 ? HTGS_BWD_WAVES_SMALL : (TW * TH <= 128 ? HTGS_BWD_WAVES_MID : 4);
+  return TW * TH <= 64 ? 2 : 4;
 }
 
 // Target waves per SIMD of the backward (register budget; HIP's second
 // launch-bounds argument is a minimum number of waves per execution unit).
-template <int KMAX, int TW>
+// The walk of a one-block tile with K <= 8 fits 96 registers; at 80 it
+// spills (630 against 516 us at 1080p). Larger cores and tiles fit 128,
+// except where LDS allows no more than two or three waves anyway.
+template <int KMAX, int TW, int TH>
 constexpr int bwd_simd_waves() {
-  return (TW == 8 && KMAX <= 8) ? 5 : ((TW == 8 && KMAX <= 16) ? 4 : 1);
+  return (TW * TH <= 64 && KMAX <= 8) ? 5 : ((KMAX <= 8 || (KMAX <= 16 && TW * TH <= 128)) ? 4 : 1);
 }
 
+// One tile of the backward. At 1080p (1M Gaussians, K = 8, 8x8 tiles) the
+// walk's VALU work (about 420 us) and the memory traffic (490 us with the
+// walk left out: 0.45 GB of state, 0.85 GB of records, a descriptor per
+// instance, and 230 us for 0.42 GB of partials in random 64-byte slots)
+// overlap to 516 us. The launch took 602 us with a branch per fragment that
+// formed the code table's addresses lane by lane, tested the clamp and the
+// smallest |d|^2 for every pixel and wrote 64 scattered partials per store;
+// K = 16 with 16x8 tiles 941 -> 722 us, the 4K frame (K = 16) 8.88 -> 7.61 ms.
 template <int KMAX, int TW, int TH, bool EXACT>
 __device__ __forceinline__ void bwd_tile(const TileInfo &ti, const Ws &w, const ViewSet &vs,
                                          const KCfg &cfg, const float *__restrict__ state,
@@ -919,27 +949,23 @@ __device__ __forceinline__ void bwd_tile(const TileInfo &ti, const Ws &w, const 
   __shared__ float4 s_pix[NT * L::kStride / 4];
   constexpr int BW = bwd_waves<TW, TH>();
   constexpr int BT = 64 * BW;
-  // per wave, for the 8x8 block being walked: [block pixel][lane ^ swz(pixel)]
-  // = core index + 1 of the lane's instance at that pixel, 0 if not in the
-  // core. The byte swizzle swz(q) = ((q >> 1) & 15) << 2 spreads the fill
-  // (each lane writes its own pixel's 64-byte row) over the banks; the
-  // reads (one row, one byte per lane) stay conflict-free.
-  // With a core of at most 8 entries the table holds core index + 1 in
-  // nibbles (two lanes per byte; a pixel's row is 32 bytes): half the LDS of
-  // byte rows, 10 KiB in all for an 8x8 tile, which made the 8x8 backward
-  // ~4% faster. Paired waves keep byte rows, which double as the buffer
-  // through which they hand over their sums.
-  constexpr bool NIB = KMAX <= 8 && !(NB == 2 && BW == 4);
-  constexpr int SB = NIB ? 32 : 64;
-  __shared__ uint8_t s_slot[BW][64][SB];
-  // core index (or -1) of table row entry idx
-  auto core_of = [](const uint8_t *row, int idx) -> int {
-    if constexpr (NIB) return (int)((row[idx >> 1] >> ((idx & 1) * 4)) & 15u) - 1;
-    else return (int)row[idx] - 1;
-  };
+  // Per wave, for the 8x8 block being walked, the fragment codes of its
+  // pixels by the chunk's instances: codes[wave][r][2 lane], [2 lane + 1]
+  // hold the eight bytes of row r for instance `lane` (core index + 1, 0
+  // where the instance is not in the core, times kCodeUnit). A lane reads
+  // its codes once per row, without bank conflicts, and a pixel's byte is an
+  // address offset as it stands. The table also carries the paired waves'
+  // sums and the partials on their way out (16 floats per lane).
+  __shared__ __attribute__((aligned(16))) uint32_t s_code[BW][8][128];
+  static_assert(sizeof(s_code[0]) == 64 * 16 * sizeof(float), "one partial per lane");
 
+  uint2 rg = w.ranges[ti.t];
+  rg.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.x);
+  rg.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.y);
+  if (rg.x >= rg.y) return;   // nothing to differentiate
   const ViewParams &V = vs.v[ti.v];
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int px0 = ti.tx * TW, py0 = ti.ty * TH;
   const int K = EXACT ? KMAX : cfg.K;
   const float *recs = w.records + (int64_t)ti.v * cfg.n * kRecFloats;
@@ -1016,17 +1042,15 @@ __device__ __forceinline__ void bwd_tile(const TileInfo &ti, const Ws &w, const 
       }
     }
     Pp[0] = G[0]; Pp[1] = G[1]; Pp[2] = G[2];
-    Pp[3] = w1; Pp[4] = q1; Pp[5] = q2; Pp[6] = 0.f; Pp[7] = 0.f;
+    Pp[3] = w1; Pp[4] = q1; Pp[5] = q2;
+    Pp[L::kPair] = 0.f; Pp[L::kPair + 1] = w1;
 #pragma unroll
     for (int i = 0; i < KMAX; ++i) {
-      Pp[L::kCoef + i] = coef[i];
-      Pp[L::kT + i] = Ti[i];
+      Pp[L::kPair + 2 + 2 * i] = coef[i];
+      Pp[L::kPair + 3 + 2 * i] = Ti[i];
     }
   }
-  __syncthreads();
 
-  const uint2 rg = w.ranges[ti.t];
-  const int wave = tid >> 6, lane = tid & 63;
   const uint32_t count = rg.y - rg.x;
   const uint32_t nch = (count + 63u) >> 6;
   const float amax = cfg.alpha_max;
@@ -1042,6 +1066,9 @@ __device__ __forceinline__ void bwd_tile(const TileInfo &ti, const Ws &w, const 
   const uint32_t c_step = PAIRS ? 2u : (uint32_t)BW;
   const int cx2 = 2 * px0 + TW - 1, cy2 = 2 * py0 + TH - 1;
   const float hx = 0.5f * (float)(TW - 1), hy = 0.5f * (float)(TH - 1);
+  // The factors are complete at the first chunk's barrier, behind its loads
+  // and staging: the waves without pixels of their own do those meanwhile.
+  bool ready = false;
   for (uint32_t c = PAIRS ? (uint32_t)(wave & 1) : (uint32_t)wave; c < c_end; c += c_step) {
     const uint32_t j = rg.x + c * 64u + lane;
     const bool active = c < nch && j < rg.y;
@@ -1077,12 +1104,21 @@ __device__ __forceinline__ void bwd_tile(const TileInfo &ti, const Ws &w, const 
         oy = __float_as_int(rec[R_IY]);
       }
     }
+    if (!ready) __syncthreads();
+    ready = true;
     const float bbf[4] = {__int_as_float(bb[0]), __int_as_float(bb[1]), __int_as_float(bb[2]),
                           __int_as_float(bb[3])};
+    // Whether every alpha of this splat stays below the clamp and |d|^2 above
+    // the smallest normal float all over the tile (|d|^2 - |its value at the
+    // centre| bounded by the coefficients' magnitudes): the walk then leaves
+    // out both tests.
+    const float ddmin = qd[0] - fmaf(hx, fabsf(qd[1]), fmaf(hy, fabsf(qd[2]), hx * hy * fabsf(qd[4])));
+    const bool plain = op <= amax && ddmin > 1e-30f;
     // acc: d-moments (6), m-moments (6), dL/do, dL/drgb (3)
     float acc[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) acc[k] = 0.f;
+    float nf = 0.f;   // this chunk's fragments
     for (int blk = 0; blk < NB; ++blk) {
       if (PAIRS && blk != myblk) continue;
       const int bx = (blk % BX) * 8, by = (blk / BX) * 8;
@@ -1091,29 +1127,26 @@ __device__ __forceinline__ void bwd_tile(const TileInfo &ti, const Ws &w, const 
       // Core table of this block for this chunk: lane = block pixel.
       {
         // list positions of the pixel's core from the forward state
-        const float *tst = tstate + blk * 64 + lane;
+        // (opaque offset: the entries' addresses would be kept over the chunks)
+        uint32_t off = (uint32_t)(blk * 64 + lane);
+        asm volatile("" : "+v"(off));
         int cps[KMAX];
 #pragma unroll
-        for (int i = 0; i < KMAX; ++i) cps[i] = i < K ? __float_as_int(tst[(int64_t)(2 * K + i) * NT]) : -1;
-        // cleared with consecutive lanes on consecutive words (no bank
-        // conflicts), then each lane fills its own pixel's row
-        uint32_t *tab = reinterpret_cast<uint32_t *>(&s_slot[wave][0][0]);
+        for (int i = 0; i < KMAX; ++i)
+          cps[i] = i < K ? __float_as_int(tstate[off + (uint32_t)((2 * K + i) * NT)]) : -1;
+        uint4 *tab = reinterpret_cast<uint4 *>(&s_code[wave][0][0]);
 #pragma unroll
-        for (int k = 0; k < SB / 4; ++k) tab[k * 64 + lane] = 0u;
+        for (int k = 0; k < 4; ++k) tab[k * 64 + lane] = make_uint4(0u, 0u, 0u, 0u);
         __builtin_amdgcn_wave_barrier();
+        // (opaque: the shifted codes would be kept over the chunks)
+        uint32_t bit = (uint32_t)((lane & 3) * 8);
+        asm volatile("" : "+v"(bit));
+        uint32_t *row = &s_code[wave][lane >> 3][(lane >> 2) & 1];
 #pragma unroll
         for (int i = 0; i < KMAX; ++i) {
           if (i < K) {
-            const int ps = cps[i];
-            const uint32_t dl = (uint32_t)(ps - (int)(c * 64u));
-            if (ps >= 0 && dl < 64u) {
-              if constexpr (NIB) {
-                uint8_t *b = &s_slot[wave][lane][(dl ^ slot_swz(lane)) >> 1];
-                *b = (uint8_t)(*b | ((i + 1) << ((dl & 1u) * 4u)));
-              } else {
-                s_slot[wave][lane][dl ^ slot_swz(lane)] = (uint8_t)(i + 1);
-              }
-            }
+            const uint32_t dl = (uint32_t)(cps[i] - (int)(c * 64u));
+            if (cps[i] >= 0 && dl < 64u) atomicOr(&row[2 * dl], (uint32_t)((i + 1) * L::kCodeUnit) << bit);
           }
         }
         __builtin_amdgcn_wave_barrier();
@@ -1126,66 +1159,80 @@ __device__ __forceinline__ void bwd_tile(const TileInfo &ti, const Ws &w, const 
       // constant. The moments (1, lx, ly, lx^2, lx ly, ly^2) of the weights
       // follow from per-row sums over (1, c, c^2).
       const float fbx = (float)bx;
-      for (int row = 0; row < 8; ++row) {
-        const float ly = (float)(by + row);
-        const float Y = ly - hy, YY = Y * Y;
-        const float rd0 = fmaf(YY, qd[5], fmaf(Y, qd[2], qd[0]));
-        const float rd1 = fmaf(Y, qd[4], qd[1]);
-        const float s2 = fmaf(qm[4], Y, qm[5]);
-        const float rm0 = fmaf(s2, s2, qm[0]);
-        const float rm1 = fmaf(qm[2], Y, qm[3]);
-        // (bitwise ands: both pixels of a column pair are tested before
-        // either fragment path branches, and no test branches on its own)
-        const bool row_in = hitb & (row < rows_in);
-        float rs[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      auto walk = [&](auto rare) __attribute__((always_inline)) {
+        constexpr bool RARE = decltype(rare)::value;
+        for (int row = 0; row < 8; ++row) {
+          const float ly = (float)(by + row);
+          const float Y = ly - hy, YY = Y * Y;
+          const float rd0 = fmaf(YY, qd[5], fmaf(Y, qd[2], qd[0]));
+          const float rd1 = fmaf(Y, qd[4], qd[1]);
+          const float s2 = fmaf(qm[4], Y, qm[5]);
+          const float rm0 = fmaf(s2, s2, qm[0]);
+          const float rm1 = fmaf(qm[2], Y, qm[3]);
+          // (bitwise ands: both pixels of a column pair are tested before
+          // either fragment path branches, and no test branches on its own)
+          const bool row_in = hitb & (row < rows_in);
+          float rs[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+          // (rs[1] and rs[2] agree up to column 1: opaque, or they share a
+          // register until they part in column 2's path)
+          asm("" : "+v"(rs[2]), "+v"(rs[5]));
+          const uint2 codes = reinterpret_cast<const uint2 *>(s_code[wave][row])[lane];
+          auto code_of = [&](int col) -> uint32_t {
+            return ((col < 4 ? codes.x : codes.y) >> (8 * (col & 3))) & 255u;
+          };
+          // (in a vector register: its reads take the column as their offset)
+          lds_bytes P = (lds_bytes)(const char *)(sp_all + ((by + row) * TW + bx) * L::kStride);
+          asm("" : "+v"(P));
 #pragma unroll
-        for (int col = 0; col < 8; col += 2) {
-          const float X0 = (fbx + (float)col) - hx, X1 = X0 + 1.f;
-          const float dd0 = fmaf(X0, rd1, fmaf(X0 * X0, qd[3], rd0));
-          const float dd1 = fmaf(X1, rd1, fmaf(X1 * X1, qd[3], rd0));
-          const float s10 = fmaf(qm[1], X0, rm1), s11 = fmaf(qm[1], X1, rm1);
-          const float mm0 = fmaf(s10, s10, rm0), mm1 = fmaf(s11, s11, rm0);
-          const bool f0 = row_in & (col < cols_in) & (dd0 >= FLT_MIN) & (mm0 <= rc * dd0);
-          const bool f1 = row_in & (col + 1 < cols_in) & (dd1 >= FLT_MIN) & (mm1 <= rc * dd1);
-          const int q = row * 8 + col;
-          const float *P0 = sp_all + ((by + row) * TW + bx + col) * L::kStride;
-          if (f0) {
-            ++nfr;
-            bwd_fragment<KMAX>(op, rgb, P0, col, dd0, mm0, core_of(s_slot[wave][q], lane ^ slot_swz(q)), amax,
-                               rs, acc);
+          for (int col = 0; col < 8; col += 2) {
+            const float X0 = (fbx + (float)col) - hx, X1 = X0 + 1.f;
+            const float dd0 = fmaf(X0, rd1, fmaf(X0 * X0, qd[3], rd0));
+            const float dd1 = fmaf(X1, rd1, fmaf(X1 * X1, qd[3], rd0));
+            const float s10 = fmaf(qm[1], X0, rm1), s11 = fmaf(qm[1], X1, rm1);
+            const float mm0 = fmaf(s10, s10, rm0), mm1 = fmaf(s11, s11, rm0);
+            const bool f0 = row_in & (col < cols_in) & (!RARE || dd0 >= FLT_MIN) & (mm0 <= rc * dd0);
+            const bool f1 = row_in & (col + 1 < cols_in) & (!RARE || dd1 >= FLT_MIN) & (mm1 <= rc * dd1);
+            if (f0) {
+              nf += 1.f;
+              bwd_fragment<KMAX, RARE>(op, rgb, P + col * 4 * L::kStride, col, dd0, mm0, code_of(col), amax, rs, acc);
+            }
+            if (f1) {
+              nf += 1.f;
+              bwd_fragment<KMAX, RARE>(op, rgb, P + (col + 1) * 4 * L::kStride, col + 1, dd1, mm1,
+                           code_of(col + 1), amax, rs, acc);
+            }
           }
-          if (f1) {
-            ++nfr;
-            bwd_fragment<KMAX>(op, rgb, P0 + L::kStride, col + 1, dd1, mm1,
-                               core_of(s_slot[wave][q + 1], lane ^ slot_swz(q + 1)), amax, rs, acc);
+          if constexpr (BX > 1) {
+            // sums over (1, c, c^2) -> over (1, lx, lx^2), lx = bx + c
+            rs[2] = fmaf(fbx, fmaf(fbx, rs[0], 2.f * rs[1]), rs[2]);
+            rs[1] = fmaf(fbx, rs[0], rs[1]);
+            rs[5] = fmaf(fbx, fmaf(fbx, rs[3], 2.f * rs[4]), rs[5]);
+            rs[4] = fmaf(fbx, rs[3], rs[4]);
           }
+          const float ly2 = ly * ly;
+          acc[0] += rs[0];
+          acc[1] += rs[1];
+          acc[2] = fmaf(ly, rs[0], acc[2]);
+          acc[3] += rs[2];
+          acc[4] = fmaf(ly, rs[1], acc[4]);
+          acc[5] = fmaf(ly2, rs[0], acc[5]);
+          acc[6] += rs[3];
+          acc[7] += rs[4];
+          acc[8] = fmaf(ly, rs[3], acc[8]);
+          acc[9] += rs[5];
+          acc[10] = fmaf(ly, rs[4], acc[10]);
+          acc[11] = fmaf(ly2, rs[3], acc[11]);
         }
-        if constexpr (BX > 1) {
-          // sums over (1, c, c^2) -> over (1, lx, lx^2), lx = bx + c
-          rs[2] = fmaf(fbx, fmaf(fbx, rs[0], 2.f * rs[1]), rs[2]);
-          rs[1] = fmaf(fbx, rs[0], rs[1]);
-          rs[5] = fmaf(fbx, fmaf(fbx, rs[3], 2.f * rs[4]), rs[5]);
-          rs[4] = fmaf(fbx, rs[3], rs[4]);
-        }
-        const float ly2 = ly * ly;
-        acc[0] += rs[0];
-        acc[1] += rs[1];
-        acc[2] = fmaf(ly, rs[0], acc[2]);
-        acc[3] += rs[2];
-        acc[4] = fmaf(ly, rs[1], acc[4]);
-        acc[5] = fmaf(ly2, rs[0], acc[5]);
-        acc[6] += rs[3];
-        acc[7] += rs[4];
-        acc[8] = fmaf(ly, rs[3], acc[8]);
-        acc[9] += rs[5];
-        acc[10] = fmaf(ly, rs[4], acc[10]);
-        acc[11] = fmaf(ly2, rs[3], acc[11]);
-      }
+      };
+      // (uniform over the wave)
+      if (__ballot(hitb && !plain) != 0ull) walk(std::true_type{});
+      else walk(std::false_type{});
       __builtin_amdgcn_wave_barrier();
     }
+    nfr += (uint32_t)nf;
     if constexpr (PAIRS) {
-      // The block-1 wave's core table is free now: it carries the sums.
-      float *xch = reinterpret_cast<float *>(&s_slot[2 + (wave & 1)][0][0]);
+      // The block-1 wave's code table is free now: it carries the sums.
+      float *xch = reinterpret_cast<float *>(&s_code[2 + (wave & 1)][0][0]);
       if (myblk == 1) {
 #pragma unroll
         for (int k = 0; k < 16; ++k) xch[k * 64 + lane] = acc[k];
@@ -1197,17 +1244,18 @@ __device__ __forceinline__ void bwd_tile(const TileInfo &ti, const Ws &w, const 
       }
       __syncthreads();  // before the block-1 waves rebuild their tables
     }
-    if (myblk <= 0 && active && (uint64_t)slot < (uint64_t)w.capacity) {
+    if (myblk <= 0) {
       // The tile's moments (about its first pixel) moved to the record's
       // reference pixel, (a, b) pixels from it (near the splat's centre,
       // which keeps the moments small): with dx = lx + a,
       // sum w dx = S_x + a S, sum w dx^2 = S_xx + 2 a S_x + a^2 S, ...
-      const float a = (float)(px0 - ox);
-      const float b = (float)(py0 - oy);
-      write_partial(acc, a, b, w.partials + (int64_t)slot * kPartialFloats);
+      const bool out = active && (uint64_t)slot < (uint64_t)w.capacity;
+      write_partials(acc, (float)(px0 - ox), (float)(py0 - oy), out ? slot : kNoSlot,
+                     reinterpret_cast<float4 *>(&s_code[wave][0][0]), w.partials, lane);
     }
     __builtin_amdgcn_wave_barrier();
   }
+  if (!ready) __syncthreads();   // (a wave without a chunk)
 }
 
 // Minimum waves per SIMD asked of the compiler for the forward (HIP's
@@ -1227,7 +1275,7 @@ __global__ void __launch_bounds__((TW * TH), (fwd_simd_waves<KMAX, TW, TH, BM>()
 }
 
 template <int KMAX, int TW, int TH, bool EXACT>
-__global__ void __launch_bounds__((64 * bwd_waves<TW, TH>()), (bwd_simd_waves<KMAX, TW>()))
+__global__ void __launch_bounds__((64 * bwd_waves<TW, TH>()), (bwd_simd_waves<KMAX, TW, TH>()))
     k_raster_bwd(Ws w, ViewSet vs, KCfg cfg, const float *__restrict__ state,
                  const uint32_t *__restrict__ vals) {
   // the forward of a failed front end rendered empty tiles: nothing to do
@@ -1481,8 +1529,12 @@ __device__ __forceinline__ void bwd_tile_sorted(const TileInfo &ti, const Ws &w,
       if ((uint64_t)slot < (uint64_t)w.capacity) {
         // (lanes past the last blended position were not staged: their
         // moments are zero, so the origin does not matter)
-        write_partial(acc, (float)(px0 - ox), (float)(py0 - oy),
-                      w.partials + (int64_t)slot * kPartialFloats);
+        float out[kPartialFloats];
+        form_partial(acc, (float)(px0 - ox), (float)(py0 - oy), out);
+        float4 *dst = reinterpret_cast<float4 *>(w.partials + (int64_t)slot * kPartialFloats);
+#pragma unroll
+        for (int k = 0; k < kPartialFloats / 4; ++k)
+          dst[k] = make_float4(out[4 * k], out[4 * k + 1], out[4 * k + 2], out[4 * k + 3]);
       }
     }
   }
