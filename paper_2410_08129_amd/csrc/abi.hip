@@ -37,7 +37,7 @@ struct Layout {
   int64_t sort_cnt, dcnt, records, rects, tslots, refpix, cflags, order, keys0, keys1, vals0, vals1;
   int64_t partials, dkeys0, dkeys1, dvals0, dvals1, bytes;
   int64_t capacity, chunk_stride, dchunk_stride;
-  int32_t key_bits, passes, key16, sorted;
+  int32_t key_bits, passes, digit_bits, key16, sorted;
 };
 
 int bits_for(int64_t tiles) {
@@ -57,7 +57,9 @@ Layout make_layout(int64_t n, int n_views, int64_t total_tiles, int64_t capacity
   L.dchunk_stride = sorted ? (n + kSortChunk - 1) / kSortChunk : 0;
   L.dchunk_stride = (L.dchunk_stride + 63) / 64 * 64;
   L.key_bits = bits_for(total_tiles);
-  L.passes = (L.key_bits + 7) / 8;
+  L.passes = sort_pass_count(L.key_bits);
+  L.digit_bits = sort_digit_bits(L.key_bits);
+  const int64_t radix = sort_radix(L.digit_bits);
   L.key16 = L.key_bits <= 16;
   L.chunk_stride = ((capacity + kSortChunk - 1) / kSortChunk + 63) / 64 * 64;
   const int64_t kb = L.key16 ? 2 : 4;
@@ -66,12 +68,12 @@ Layout make_layout(int64_t n, int n_views, int64_t total_tiles, int64_t capacity
   L.total = o; o = align_up(o + 8);   // instance count
   L.frags = o; o = align_up(o + 2 * 8 * kCounterSpread * kCounterStride);  // fragment counters
   L.pp_total = o; o = align_up(o + 8 * ((n + kPreThreads - 1) / kPreThreads));
-  L.hist = o; o = align_up(o + kHistCopies * 4 * 256 * 4);
+  L.hist = o; o = align_up(o + kHistCopies * L.passes * radix * 4);
   L.ranges = o; o = align_up(o + 8 * total_tiles);
   L.order_hist = o; o = align_up(o + 2 * 32 * 4);
   L.dhist = o; o = align_up(o + (sorted ? kHistCopies * 4 * 256 * 4 : 0));
   L.zero_end = o;
-  L.sort_cnt = o; o = align_up(o + (int64_t)L.passes * 256 * L.chunk_stride * 4);
+  L.sort_cnt = o; o = align_up(o + (int64_t)L.passes * radix * L.chunk_stride * 4);
   L.dcnt = o; o = align_up(o + 4 * 256 * L.dchunk_stride * 4);
   L.records = o; o = align_up(o + (int64_t)n_views * n * kRecFloats * 4);
   L.rects = o; o = align_up(o + (int64_t)n_views * n * 16);
@@ -144,6 +146,7 @@ Ws make_ws(void *base, const Layout &L) {
   w.chunk_stride = L.chunk_stride;
   w.key_bits = L.key_bits;
   w.passes = L.passes;
+  w.digit_bits = L.digit_bits;
   w.key16 = L.key16;
   w.final_buf = L.passes & 1;
   return w;

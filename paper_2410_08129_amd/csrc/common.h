@@ -102,8 +102,8 @@ struct Ws {
   unsigned long long *frags;   // fragments counted by the forward raster (spread, below)
   unsigned long long *frags_bwd;  // fragments counted by the backward raster (spread)
   unsigned long long *pp_total;  // per preprocess workgroup: its instance total, then its first slot
-  uint32_t *hist;              // [kHistCopies][4][256] digit histograms (summed when read)
-  uint32_t *sort_cnt;          // [passes][256][chunk_stride]: per-chunk digit counts, then
+  uint32_t *hist;              // [kHistCopies][passes][radix] digit histograms (summed when read)
+  uint32_t *sort_cnt;          // [passes][radix][chunk_stride]: per-chunk digit counts, then
                                // the global start of each (digit, chunk) run
   uint2 *ranges;               // [total_tiles] (start, end)
   uint32_t *order_hist;        // [2][32] cost-bucket counts and cursors
@@ -122,13 +122,13 @@ struct Ws {
   // preprocess walks), its digit histograms and per-chunk counts.
   uint32_t *dkeys[2];
   uint32_t *dvals[2];
-  uint32_t *dhist;             // [kHistCopies][4][256]
+  uint32_t *dhist;             // [kHistCopies][4][256] (four passes of 8 bits)
   uint32_t *dcnt;              // [4][256][dchunk_stride]
   const uint32_t *perm;        // Gaussians front to back (null: index order)
   int64_t dchunk_stride;
   int64_t capacity;
   int64_t chunk_stride;        // words per digit row of sort_cnt (>= chunks of capacity)
-  int32_t key_bits, passes, key16;
+  int32_t key_bits, passes, digit_bits, key16;   // passes of digit_bits (the last maybe fewer)
   int32_t final_buf;           // which of keys/vals holds the sorted lists
 };
 
@@ -146,22 +146,37 @@ constexpr int kSortedStateValues = 7;
 // emit launch's end-of-workgroup adds (one per non-empty digit, ~24 per
 // workgroup) queued on 16 cache lines and set its length (87 us at 1080p).
 constexpr int kHistCopies = 64;
-__device__ __forceinline__ uint32_t *hist_copy(uint32_t *hist) {
-  return hist + (blockIdx.x % kHistCopies) * (4 * 256);
+// Copy of a histogram of `words` digits (over all passes) that this
+// workgroup adds to.
+__device__ __forceinline__ uint32_t *hist_copy(uint32_t *hist, int words) {
+  return hist + (blockIdx.x % kHistCopies) * words;
 }
 
-// LDS digit histogram of one wave's keys, in C copies of kHistPadWords
-// words (copy c at c * kHistPadWords, so that the copies of a digit lie in
-// different banks): for digits of at most two bits, one ballot per digit
+// Radix sort digits: 8 bits at most, the passes as even as possible; 9 bits
+// where that saves a pass and a table of 512 entries is used at most twice
+// (9, 17 and 18 bits: the tiles of a 3840x2160 frame, or of a batch of
+// views). On that frame's 102M instances two passes of 9 and 8 bits take
+// 1.21 ms where three of 8, 8 and 1 took 1.54.
+constexpr int kMaxPasses = 4;
+__host__ __device__ constexpr int sort_pass_count(int key_bits) {
+  return key_bits == 9 ? 1 : (key_bits == 17 || key_bits == 18) ? 2 : (key_bits + 7) / 8;
+}
+__host__ __device__ constexpr int sort_digit_bits(int key_bits) {
+  return (key_bits + sort_pass_count(key_bits) - 1) / sort_pass_count(key_bits);
+}
+constexpr int kMaxDigitBits = 9;
+__host__ __device__ constexpr int sort_radix(int digit_bits) { return digit_bits > 8 ? 512 : 256; }
+
+// LDS digit histogram of one wave's keys, in C copies of R + 1 words (copy c
+// at c (R + 1), so that the copies of a digit lie in different banks): for digits of at most two bits, one ballot per digit
 // value and one add each; otherwise one add per lane into copy lane % C.
 // Lanes of one wave that add to one address are served one after another,
 // and tile keys often share their high digits across a wave (one add per
 // lane on one copy made the high passes' counting many times slower; a
 // test for a wave whose keys all share one digit cost more than it saved).
 // Called by all lanes of the wave.
-constexpr int kHistLaneCopies = 4, kHistPadWords = 257;
-constexpr int kHistWords = kHistLaneCopies * kHistPadWords;
-template <int C = kHistLaneCopies>
+constexpr int kHistLaneCopies = 4;
+template <int R, int C = kHistLaneCopies>
 __device__ __forceinline__ void wave_hist_add(uint32_t *h, uint32_t d, bool valid, int nbits) {
   const uint64_t vm = __ballot(valid);
   if (vm == 0ull) return;
@@ -174,22 +189,16 @@ __device__ __forceinline__ void wave_hist_add(uint32_t *h, uint32_t d, bool vali
     }
     return;
   }
-  if (valid) atomicAdd(&h[(lane % C) * kHistPadWords + d], 1u);
+  if (valid) atomicAdd(&h[(lane % C) * (R + 1) + d], 1u);
 }
-// Digit d of a histogram written by wave_hist_add<C>.
-template <int C = kHistLaneCopies>
+// Digit d of a histogram written by wave_hist_add<R, C>.
+template <int R, int C = kHistLaneCopies>
 __device__ __forceinline__ uint32_t hist_total(const uint32_t *h, int d) {
   uint32_t t = 0;
 #pragma unroll
-  for (int c = 0; c < C; ++c) t += h[c * kHistPadWords + d];
+  for (int c = 0; c < C; ++c) t += h[c * (R + 1) + d];
   return t;
 }
-// Width of sort pass p's digit for keys of key_bits bits.
-__host__ __device__ __forceinline__ int pass_bits(int key_bits, int p) {
-  const int r = key_bits - 8 * p;
-  return r < 8 ? r : 8;
-}
-
 // Fragment counters: kCounterSpread words, each in a 128-byte line of its
 // own, added to by workgroup blockIdx % kCounterSpread and summed when
 // read. With one word, the raster's tens of thousands of workgroups queued

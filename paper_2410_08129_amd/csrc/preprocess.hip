@@ -693,7 +693,8 @@ __global__ void __launch_bounds__(kTotScanThreads) k_preprocess_scan(Ws w, int64
 // s_start holds the workgroup-relative first slot of every (group, view,
 // lane), in slot order, plus the workgroup total at the end; it first holds
 // the counts. The tile-slot descriptors get their first slots here.
-template <bool MV>
+// R: entries of the digit tables.
+template <bool MV, int R>
 __global__ void __launch_bounds__(kPreThreads) k_emit(KCfg cfg, ViewSet vs, Ws w) {
   constexpr int NVL = MV ? kMaxViews : 1;
   __shared__ uint32_t s_start[NVL * kPreThreads + 1];
@@ -701,14 +702,15 @@ __global__ void __launch_bounds__(kPreThreads) k_emit(KCfg cfg, ViewSet vs, Ws w
   __shared__ unsigned long long s_vmask[NVL][kPreThreads];
   // (the batched form's per-view tables leave room for one copy)
   constexpr int HC = MV ? 1 : kHistLaneCopies;
-  __shared__ uint32_t s_hist[4][HC * kHistPadWords];
+  constexpr int NP = R == 512 ? 2 : kMaxPasses;   // (9-bit digits: at most two)
+  __shared__ uint32_t s_hist[NP][HC * (R + 1)];
   __shared__ uint32_t s_wsum[kPreThreads / 64];
   __shared__ uint32_t s_gidx[kPreThreads];
   __shared__ uint32_t s_mark[kPreThreads / 64][64];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t blk = blockIdx.x;
-  for (int i = tid; i < 4 * HC * kHistPadWords; i += kPreThreads) (&s_hist[0][0])[i] = 0u;
+  for (int i = tid; i < w.passes * HC * (R + 1); i += kPreThreads) (&s_hist[0][0])[i] = 0u;
   int64_t g;
   const bool live = gaussian_at(w, cfg, blk * kPreThreads + tid, g);
   s_gidx[tid] = (uint32_t)g;
@@ -837,18 +839,21 @@ __global__ void __launch_bounds__(kPreThreads) k_emit(KCfg cfg, ViewSet vs, Ws w
     // wave_hist_add cost the emit more than the conflicts they avoid)
     if (valid)
       for (int p = 0; p < w.passes; ++p)
-        atomicAdd(&s_hist[p][(lane % HC) * kHistPadWords + ((key >> (8 * p)) & 255u)], 1u);
+        atomicAdd(&s_hist[p][(lane % HC) * (R + 1) +
+                             ((key >> (w.digit_bits * p)) & ((1u << w.digit_bits) - 1u))], 1u);
     if (valid && e < room) {
       if (w.key16) k16[base + e] = (uint16_t)key; else k32[base + e] = key;
       w.vals[0][base + e] = gid;
     }
   }
   __syncthreads();
-  uint32_t *hist = hist_copy(w.hist);
-  for (int p = 0; p < w.passes; ++p) {
-    const uint32_t c = hist_total<HC>(s_hist[p], tid);
-    if (c) atomicAdd(&hist[p * 256 + tid], c);
-  }
+  uint32_t *hist = hist_copy(w.hist, w.passes * R);
+  for (int p = 0; p < w.passes; ++p)
+#pragma unroll
+    for (int d = tid; d < R; d += kPreThreads) {
+      const uint32_t c = hist_total<R, HC>(s_hist[p], d);
+      if (c) atomicAdd(&hist[p * R + d], c);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1357,10 +1362,10 @@ hipError_t launch_preprocess(const GaussPtrs &gp, const KCfg &cfg, const ViewSet
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_preprocess_scan, dim3(1), dim3(kTotScanThreads), 0, s, w, (int64_t)blocks);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (vs.n > 1)
-    hipLaunchKernelGGL(k_emit<true>, dim3(blocks), dim3(kPreThreads), 0, s, cfg, vs, w);
-  else
-    hipLaunchKernelGGL(k_emit<false>, dim3(blocks), dim3(kPreThreads), 0, s, cfg, vs, w);
+  const bool wide = sort_radix(w.digit_bits) == 512;
+  auto *emit = vs.n > 1 ? (wide ? k_emit<true, 512> : k_emit<true, 256>)
+                        : (wide ? k_emit<false, 512> : k_emit<false, 256>);
+  hipLaunchKernelGGL(emit, dim3(blocks), dim3(kPreThreads), 0, s, cfg, vs, w);
   return hipGetLastError();
 }
 

@@ -4,10 +4,10 @@
 // blending (the 3DGS order that the paper's "w/o per-pixel HT"
 // configuration blends in, Sec. 4.3, Table splat_eval).
 //
-// Three launches per 8-bit digit, none of whose workgroups waits for
-// another. The keys are cut into chunks of 4096 in list order.
+// Three launches per digit of at most 9 bits, none of whose workgroups waits
+// for another. The keys are cut into chunks of 4096 in list order.
 //   count:   each workgroup counts the digits of its chunk (LDS adds) and
-//            stores the 256 counts into a digit-major table;
+//            stores the counts into a digit-major table;
 //   scan:    one workgroup per digit turns its row of chunk counts into the
 //            global start of the digit's run from each chunk (the digit's
 //            base is the sum of the smaller digits' totals, which the
@@ -35,10 +35,11 @@ struct SortJob {
   const unsigned long long *count;  // null: n_fixed items
   uint64_t n_fixed;
   int64_t capacity;
-  const uint32_t *hist;             // [kHistCopies][4][256]
-  uint32_t *cnt;                    // [passes][256][stride]: digit counts per chunk, then
+  const uint32_t *hist;             // [kHistCopies][passes][radix]
+  uint32_t *cnt;                    // [passes][radix][stride]: digit counts per chunk, then
                                     // the global start of each (digit, chunk) run
   int64_t stride;
+  int32_t passes, digit_bits;
 };
 
 // Items to sort, or false on overflow, when only part of the keys exist
@@ -64,7 +65,7 @@ __device__ __forceinline__ uint64_t chunk_of(uint64_t b, uint64_t nchunks) {
 __device__ __forceinline__ uint64_t match_digit(uint32_t d, uint64_t valid, int nbits) {
   uint32_t xlo = 0u, xhi = 0u;
 #pragma unroll
-  for (int b = 0; b < 8; ++b) {
+  for (int b = 0; b < kMaxDigitBits; ++b) {
     if (b < nbits) {  // uniform
       const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);  // all ones where set
       const uint64_t bal = __ballot((int32_t)m < 0);
@@ -75,7 +76,9 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, uint64_t valid, int 
   return valid & ~(((uint64_t)xhi << 32) | (uint64_t)xlo);
 }
 
-__device__ __forceinline__ uint32_t digit_of(uint32_t key, int shift) { return (key >> shift) & 255u; }
+__device__ __forceinline__ uint32_t digit_of(uint32_t key, int shift, int nbits) {
+  return __builtin_amdgcn_ubfe(key, (uint32_t)shift, (uint32_t)nbits);
+}
 
 // Inclusive sum over the lanes of a wave by DPP moves (shifts by 1, 2, 4, 8
 // inside each row of 16 lanes, then the row ends broadcast to the rows
@@ -102,10 +105,10 @@ __device__ __forceinline__ T load_at(const T *base, uint32_t i) {
                                       (uint32_t)(i * (uint32_t)sizeof(T)));
 }
 
-template <typename KeyT>
+template <typename KeyT, int R>
 __global__ void __launch_bounds__(kSortThreads) k_sort_count(SortJob job, int pass, int nbits,
                                                               const KeyT *__restrict__ kin) {
-  __shared__ uint32_t s_cnt[kHistWords];
+  __shared__ uint32_t s_cnt[kHistLaneCopies * (R + 1)];
   uint64_t I;
   if (!sort_items(job, I)) return;
   const uint64_t nchunks = (I + kSortChunk - 1) / kSortChunk;
@@ -113,8 +116,8 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_count(SortJob job, int pa
   const uint64_t chunk = chunk_of(blockIdx.x, nchunks);
   const uint64_t cbase = chunk * kSortChunk;
   const int tid = threadIdx.x;
-  for (int i = tid; i < kHistWords; i += kSortThreads) s_cnt[i] = 0u;
-  const int shift = 8 * pass;
+  for (int i = tid; i < kHistLaneCopies * (R + 1); i += kSortThreads) s_cnt[i] = 0u;
+  const int shift = job.digit_bits * pass;
   uint32_t dg[kSortItems];
   const bool whole = cbase + kSortChunk <= I;
   if (whole) {
@@ -128,10 +131,10 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_count(SortJob job, int pa
 #pragma unroll
       for (int h = 0; h < 4; ++h) {
         if constexpr (sizeof(KeyT) == 2) {
-          dg[j * kPer + 2 * h] = digit_of(u[h] & 0xffffu, shift);
-          dg[j * kPer + 2 * h + 1] = digit_of(u[h] >> 16, shift);
+          dg[j * kPer + 2 * h] = digit_of(u[h] & 0xffffu, shift, nbits);
+          dg[j * kPer + 2 * h + 1] = digit_of(u[h] >> 16, shift, nbits);
         } else {
-          dg[j * kPer + h] = digit_of(u[h], shift);
+          dg[j * kPer + h] = digit_of(u[h], shift, nbits);
         }
       }
     }
@@ -139,19 +142,22 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_count(SortJob job, int pa
 #pragma unroll
     for (int i = 0; i < kSortItems; ++i) {
       const uint64_t idx = cbase + (uint64_t)i * kSortThreads + tid;
-      dg[i] = idx < I ? digit_of((uint32_t)kin[idx], shift) : 0u;
+      dg[i] = idx < I ? digit_of((uint32_t)kin[idx], shift, nbits) : 0u;
     }
   }
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < kSortItems; ++i)
-    wave_hist_add(s_cnt, dg[i], whole || cbase + (uint64_t)i * kSortThreads + tid < I, nbits);
+    wave_hist_add<R>(s_cnt, dg[i], whole || cbase + (uint64_t)i * kSortThreads + tid < I, nbits);
   __syncthreads();
-  job.cnt[((size_t)pass * 256 + tid) * (size_t)job.stride + chunk] = hist_total(s_cnt, tid);
+#pragma unroll
+  for (int d = tid; d < R; d += kSortThreads)
+    job.cnt[((size_t)pass * R + d) * (size_t)job.stride + chunk] = hist_total<R>(s_cnt, d);
 }
 
 // One workgroup per digit: exclusive scan of its row of chunk counts, plus
 // the digit's base, in place.
+template <int R>
 __global__ void __launch_bounds__(256) k_sort_scan(SortJob job, int pass) {
   __shared__ uint32_t s_wsum[4];
   __shared__ uint32_t s_base;
@@ -162,15 +168,21 @@ __global__ void __launch_bounds__(256) k_sort_scan(SortJob job, int pass) {
   const uint32_t dg = blockIdx.x;
   // base: the totals of the digits below this one
   uint32_t x = 0u;
-  if (tid < (int)dg)
-    for (int c = 0; c < kHistCopies; ++c) x += job.hist[(c * 4 + pass) * 256 + tid];
+  const int copy = job.passes * R;
+#pragma unroll
+  for (int d0 = 0; d0 < R; d0 += 256)
+    if (d0 + tid < (int)dg) {
+      const uint32_t *h = job.hist + pass * R + d0 + tid;
+#pragma unroll
+      for (int c = 0; c < kHistCopies; ++c) x += h[c * copy];
+    }
   const uint32_t wx = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_add(x), 63);
   if (lane == 0) s_wsum[wave] = wx;
   __syncthreads();
   if (tid == 0) s_base = s_wsum[0] + s_wsum[1] + s_wsum[2] + s_wsum[3];
   __syncthreads();
   uint32_t carry = s_base;
-  uint32_t *row = job.cnt + ((size_t)pass * 256 + dg) * (size_t)job.stride;
+  uint32_t *row = job.cnt + ((size_t)pass * R + dg) * (size_t)job.stride;
   for (uint64_t c0 = 0; c0 < nchunks; c0 += 256 * kScanItems) {
     const uint64_t cb = c0 + (uint64_t)tid * kScanItems;
     uint32_t v[kScanItems];
@@ -206,15 +218,15 @@ __global__ void __launch_bounds__(256) k_sort_scan(SortJob job, int pass) {
   }
 }
 
-template <typename KeyT>
+template <typename KeyT, int R>
 __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int pass, int nbits,
                                                                 const KeyT *__restrict__ kin,
                                                                 const uint32_t *__restrict__ vin,
                                                                 KeyT *__restrict__ kout,
                                                                 uint32_t *__restrict__ vout) {
-  static_assert(kSortThreads == 256, "one thread per digit");
-  __shared__ uint32_t s_wh[kSortWaves][256];  // per wave and digit: count, then local offset
-  __shared__ uint32_t s_off[256];             // global position of local slot 0, per digit
+  constexpr int DP = R / kSortThreads;      // digits per thread, consecutive
+  __shared__ uint32_t s_wh[kSortWaves][R];  // per wave and digit: count, then local offset
+  __shared__ uint32_t s_off[R];             // global position of local slot 0, per digit
   __shared__ uint32_t s_csum[kSortWaves];
   __shared__ KeyT s_key[kSortChunk];
   __shared__ uint32_t s_val[kSortChunk];
@@ -226,15 +238,18 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int 
   const uint64_t chunk = chunk_of(blockIdx.x, nchunks);
   const uint64_t cbase = chunk * kSortChunk;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // global start of this chunk's run of digit tid (from the scan)
-  const uint32_t run_start = job.cnt[((size_t)pass * 256 + tid) * (size_t)job.stride + chunk];
-  for (int i = tid; i < kSortWaves * 256; i += kSortThreads) (&s_wh[0][0])[i] = 0u;
+  // global starts of this chunk's runs of the thread's digits (from the scan)
+  uint32_t run_start[DP];
+#pragma unroll
+  for (int q = 0; q < DP; ++q)
+    run_start[q] = job.cnt[((size_t)pass * R + tid * DP + q) * (size_t)job.stride + chunk];
+  for (int i = tid; i < kSortWaves * R; i += kSortThreads) (&s_wh[0][0])[i] = 0u;
   __syncthreads();
 
   // Items of the chunk: nv; lane l of wave w holds item w 1024 + 64 i + l
   // as its i-th (out-of-range lanes read the last item and take no part).
   const uint32_t nv = (I - cbase) < (uint64_t)kSortChunk ? (uint32_t)(I - cbase) : (uint32_t)kSortChunk;
-  const int shift = 8 * pass;
+  const int shift = job.digit_bits * pass;
   const uint32_t obase = (uint32_t)wave * (64 * kSortItems) + (uint32_t)lane;
   const KeyT *kc = kin + cbase;
   const uint32_t *vc = vin + cbase;
@@ -265,7 +280,7 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int 
 #pragma unroll
   for (int i = 0; i < kSortItems; ++i) {
     const bool valid = 64 * i < rem;
-    const uint32_t d = digit_of(kx[i], shift);
+    const uint32_t d = digit_of(kx[i], shift, nbits);
     const uint64_t peers = match_digit(d, __ballot(valid), nbits);
     const uint32_t lt = (uint32_t)__popcll(peers & lanemask_lt);
     uint32_t old = 0;
@@ -282,18 +297,24 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int 
   }
   __syncthreads();
 
-  // Per digit (thread d): the chunk's count; the local start of each digit
-  // is the exclusive scan of the counts over digits.
-  const int d = tid;
-  uint32_t cnt = 0;
+  // Per digit: the chunk's count; the local start of each digit is the
+  // exclusive scan of the counts over digits.
+  uint32_t cnt[DP], mine = 0;
 #pragma unroll
-  for (int k = 0; k < kSortWaves; ++k) cnt += s_wh[k][d];
-  const uint32_t c = wave_incl_add(cnt);
+  for (int q = 0; q < DP; ++q) {
+    cnt[q] = 0;
+#pragma unroll
+    for (int k = 0; k < kSortWaves; ++k) cnt[q] += s_wh[k][tid * DP + q];
+    mine += cnt[q];
+  }
+  const uint32_t c = wave_incl_add(mine);
   if (lane == 63) s_csum[wave] = c;
   __syncthreads();
-  uint32_t local_start = c - cnt;
+  uint32_t local_start = c - mine;
   for (int k = 0; k < wave; ++k) local_start += s_csum[k];
-  {
+#pragma unroll
+  for (int q = 0; q < DP; ++q) {
+    const int d = tid * DP + q;
     uint32_t run = local_start;
 #pragma unroll
     for (int k = 0; k < kSortWaves; ++k) {
@@ -301,9 +322,10 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int 
       s_wh[k][d] = run;
       run += v;
     }
+    // position of local slot p of digit d: run_start + (p - local_start)
+    s_off[d] = run_start[q] - local_start;
+    local_start += cnt[q];
   }
-  // position of local slot p of digit d: run_start + (p - local_start)
-  s_off[d] = run_start - local_start;
   __syncthreads();
 
   // Reorder the chunk by digit in LDS (the values are loaded only now, which
@@ -323,7 +345,7 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int 
     if (64 * i < rem) {
       uint32_t kk = kPack ? (kx[i] & 0xffffu) : kx[i];
       asm volatile("" : "+v"(kk));
-      const uint32_t lp = s_wh[wave][digit_of(kk, shift)] + rank[i];
+      const uint32_t lp = s_wh[wave][digit_of(kk, shift, nbits)] + rank[i];
       s_key[lp] = (KeyT)kk;
       s_val[lp] = val[i];
     }
@@ -332,7 +354,7 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int 
 
   for (int p = tid; p < (int)nv; p += kSortThreads) {
     const KeyT k = s_key[p];
-    const uint32_t pos = s_off[digit_of((uint32_t)k, shift)] + (uint32_t)p;
+    const uint32_t pos = s_off[digit_of((uint32_t)k, shift, nbits)] + (uint32_t)p;
     if (pos < I) {  // always, when the counts match the emitted keys
       kout[pos] = k;
       vout[pos] = s_val[p];
@@ -342,22 +364,23 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int 
 
 // The three launches of each pass; blocks: the largest chunk count the
 // item count can reach.
-template <typename KeyT>
-static hipError_t sort_passes(const SortJob &job, int passes, int key_bits, int64_t blocks,
-                              void *const *keys, uint32_t *const *vals, hipStream_t s) {
+template <typename KeyT, int R>
+static hipError_t sort_passes(const SortJob &job, int key_bits, int64_t blocks, void *const *keys,
+                              uint32_t *const *vals, hipStream_t s) {
   if (blocks < 1) blocks = 1;
-  for (int p = 0; p < passes; ++p) {
-    const int nbits = (key_bits - 8 * p) < 8 ? (key_bits - 8 * p) : 8;
+  for (int p = 0; p < job.passes; ++p) {
+    const int left = key_bits - job.digit_bits * p;
+    const int nbits = left < job.digit_bits ? left : job.digit_bits;
     const KeyT *kin = reinterpret_cast<const KeyT *>(keys[p & 1]);
     KeyT *kout = reinterpret_cast<KeyT *>(keys[(p + 1) & 1]);
-    hipLaunchKernelGGL(k_sort_count<KeyT>, dim3((uint32_t)blocks), dim3(kSortThreads), 0, s, job, p,
-                       nbits, kin);
+    hipLaunchKernelGGL((k_sort_count<KeyT, R>), dim3((uint32_t)blocks), dim3(kSortThreads), 0, s,
+                       job, p, nbits, kin);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_sort_scan, dim3(256), dim3(256), 0, s, job, p);
+    hipLaunchKernelGGL(k_sort_scan<R>, dim3(R), dim3(256), 0, s, job, p);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_sort_scatter<KeyT>, dim3((uint32_t)blocks), dim3(kSortThreads), 0, s, job,
-                       p, nbits, kin, vals[p & 1], kout, vals[(p + 1) & 1]);
+    hipLaunchKernelGGL((k_sort_scatter<KeyT, R>), dim3((uint32_t)blocks), dim3(kSortThreads), 0, s,
+                       job, p, nbits, kin, vals[p & 1], kout, vals[(p + 1) & 1]);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;
@@ -474,8 +497,12 @@ static hipError_t sort_impl(const Ws &w, hipStream_t s) {
   job.hist = w.hist;
   job.cnt = w.sort_cnt;
   job.stride = w.chunk_stride;
-  return sort_passes<KeyT>(job, w.passes, w.key_bits, (w.capacity + kSortChunk - 1) / kSortChunk,
-                           w.keys, w.vals, s);
+  job.passes = w.passes;
+  job.digit_bits = w.digit_bits;
+  const int64_t blocks = (w.capacity + kSortChunk - 1) / kSortChunk;
+  return sort_radix(w.digit_bits) == 512
+             ? sort_passes<KeyT, 512>(job, w.key_bits, blocks, w.keys, w.vals, s)
+             : sort_passes<KeyT, 256>(job, w.key_bits, blocks, w.keys, w.vals, s);
 }
 
 // Sort key of sorted blending: the view depth of the mean, the third row of
@@ -488,8 +515,9 @@ __global__ void __launch_bounds__(256) k_depth_keys(const float *__restrict__ me
                                                      uint32_t *__restrict__ keys,
                                                      uint32_t *__restrict__ idx,
                                                      uint32_t *__restrict__ hist) {
-  __shared__ uint32_t s_hist[4][kHistWords];
-  for (int i = threadIdx.x; i < 4 * kHistWords; i += blockDim.x) (&s_hist[0][0])[i] = 0u;
+  constexpr int R = 256, kWords = kHistLaneCopies * (R + 1);
+  __shared__ uint32_t s_hist[4][kWords];
+  for (int i = threadIdx.x; i < 4 * kWords; i += blockDim.x) (&s_hist[0][0])[i] = 0u;
   __syncthreads();
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   // (the trip count is uniform over the workgroup: the histogram adds are
@@ -509,12 +537,12 @@ __global__ void __launch_bounds__(256) k_depth_keys(const float *__restrict__ me
       idx[g] = (uint32_t)g;
     }
 #pragma unroll
-    for (int p = 0; p < 4; ++p) wave_hist_add(s_hist[p], (key >> (8 * p)) & 255u, valid, 8);
+    for (int p = 0; p < 4; ++p) wave_hist_add<R>(s_hist[p], (key >> (8 * p)) & 255u, valid, 8);
   }
   __syncthreads();
-  uint32_t *hc = hist_copy(hist);
-  for (int i = threadIdx.x; i < 4 * 256; i += blockDim.x) {
-    const uint32_t c = hist_total(s_hist[i >> 8], i & 255);
+  uint32_t *hc = hist_copy(hist, 4 * R);
+  for (int i = threadIdx.x; i < 4 * R; i += blockDim.x) {
+    const uint32_t c = hist_total<R>(s_hist[i >> 8], i & 255);
     if (c) atomicAdd(&hc[i], c);
   }
 }
@@ -538,8 +566,10 @@ hipError_t launch_depth_sort(const Ws &w, const float *means, int64_t n, const f
   job.hist = w.dhist;
   job.cnt = w.dcnt;
   job.stride = w.dchunk_stride;
+  job.passes = 4;
+  job.digit_bits = 8;
   void *keys[2] = {w.dkeys[0], w.dkeys[1]};
-  return sort_passes<uint32_t>(job, 4, 32, (n + kSortChunk - 1) / kSortChunk, keys, w.dvals, s);
+  return sort_passes<uint32_t, 256>(job, 32, (n + kSortChunk - 1) / kSortChunk, keys, w.dvals, s);
 }
 
 template <typename KeyT>
