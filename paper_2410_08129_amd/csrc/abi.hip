@@ -140,6 +140,7 @@ Ws make_ws(void *base, const Layout &L) {
     w.dhist = reinterpret_cast<uint32_t *>(b + L.dhist);
     w.dcnt = reinterpret_cast<uint32_t *>(b + L.dcnt);
     w.perm = w.dvals[0];   // after the four depth-sort passes
+    w.counts = w.dkeys[0];
     w.dchunk_stride = L.dchunk_stride;
   }
   w.capacity = L.capacity;

@@ -119,12 +119,13 @@ struct Ws {
   float *partials;             // [capacity][24]
   // Sorted blending: the Gaussians' mean-depth sort keys, sorted (key,
   // index) pairs (ping-pong; the final index buffer is the order the
-  // preprocess walks), its digit histograms and per-chunk counts.
+  // emit launch walks), its digit histograms and per-chunk counts.
   uint32_t *dkeys[2];
   uint32_t *dvals[2];
   uint32_t *dhist;             // [kHistCopies][4][256] (four passes of 8 bits)
   uint32_t *dcnt;              // [4][256][dchunk_stride]
   const uint32_t *perm;        // Gaussians front to back (null: index order)
+  uint32_t *counts;            // instances per Gaussian (in dkeys[0], after the depth sort)
   int64_t dchunk_stride;
   int64_t capacity;
   int64_t chunk_stride;        // words per digit row of sort_cnt (>= chunks of capacity)

@@ -582,7 +582,7 @@ __global__ void __launch_bounds__(256) k_fill_zero(uint4 *p, int64_t n16) {
     p[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
-// Position pos of the list the front end walks holds Gaussian g: the index
+// Position pos of the list the emit launch walks holds Gaussian g: the index
 // itself, or, for sorted blending, the Gaussian at that place of the
 // front-to-back order (so instances are emitted in that order, and the
 // stable tile sort keeps it inside each tile). False past the end.
@@ -598,6 +598,21 @@ __device__ __forceinline__ bool gaussian_at(const Ws &w, const KCfg &cfg, int64_
   return true;
 }
 
+// The workgroup's sum of v to *dst. All threads.
+__device__ __forceinline__ void block_total(unsigned long long v, unsigned long long *s_wsum,
+                                            unsigned long long *dst) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  if ((threadIdx.x & 63) == 0) s_wsum[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned long long t = 0;
+#pragma unroll
+    for (int k = 0; k < kPreThreads / 64; ++k) t += s_wsum[k];
+    *dst = t;
+  }
+}
+
 // Per Gaussian and view (MV: more than one view, which keeps more values
 // live; CULL: tile culling of small boxes): the record, the rect, the
 // colour flags and a tile-slot descriptor whose first word holds the
@@ -610,8 +625,8 @@ __global__ void __launch_bounds__(kPreThreads) k_preprocess(GaussPtrs gp, KCfg c
   __shared__ CullLds s_cull[CULL ? kPreThreads / 64 : 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t blk = blockIdx.x;
-  int64_t g;
-  const bool live = gaussian_at(w, cfg, blk * kPreThreads + tid, g);
+  const int64_t g = blk * kPreThreads + tid;
+  const bool live = g < cfg.n;
   const int nviews = MV ? vs.n : 1;
   unsigned long long total = 0;
   Activated a;
@@ -631,18 +646,24 @@ __global__ void __launch_bounds__(kPreThreads) k_preprocess(GaussPtrs gp, KCfg c
       w.tslots[(int64_t)v * cfg.n + g] =
           c ? make_uint4(c, packed, (uint32_t)mk, (uint32_t)(mk >> 32)) : make_uint4(0u, 0u, 0u, 0u);
       total += c;
+      if (!MV && w.perm) w.counts[g] = c;
     }
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, 64);
-  if (lane == 0) s_wsum[wave] = total;
-  __syncthreads();
-  if (tid == 0) {
-    unsigned long long t = 0;
-#pragma unroll
-    for (int k = 0; k < kPreThreads / 64; ++k) t += s_wsum[k];
-    w.pp_total[blk] = t;
-  }
+  // (sorted blending totals the workgroups of the depth order instead)
+  if (MV || !w.perm) block_total(total, s_wsum, w.pp_total + blk);
+}
+
+// Sorted blending: the instance totals of the emit launch's workgroups,
+// whose Gaussians follow in depth order. The Gaussians themselves are
+// preprocessed in index order, where their parameters and records lie side
+// by side; walking the depth order there read and wrote a line per row and
+// lane (265 us instead of 144 at 720p and 1M Gaussians, this launch
+// included).
+__global__ void __launch_bounds__(kPreThreads) k_perm_totals(KCfg cfg, Ws w) {
+  __shared__ unsigned long long s_wsum[kPreThreads / 64];
+  int64_t g;
+  const bool live = gaussian_at(w, cfg, (int64_t)blockIdx.x * kPreThreads + threadIdx.x, g);
+  block_total(live ? w.counts[g] : 0u, s_wsum, w.pp_total + blockIdx.x);
 }
 
 // Exclusive scan of the workgroup totals, in place, by one workgroup; the
@@ -1360,6 +1381,10 @@ hipError_t launch_preprocess(const GaussPtrs &gp, const KCfg &cfg, const ViewSet
 #undef HTGS_PRE3
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (w.perm) {
+    hipLaunchKernelGGL(k_perm_totals, dim3(blocks), dim3(kPreThreads), 0, s, cfg, w);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(k_preprocess_scan, dim3(1), dim3(kTotScanThreads), 0, s, w, (int64_t)blocks);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const bool wide = sort_radix(w.digit_bits) == 512;
