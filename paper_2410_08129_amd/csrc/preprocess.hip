@@ -911,6 +911,33 @@ __device__ __forceinline__ void seg_scan_step(uint32_t seg, float *v) {
   }
 }
 
+// The same step for finite values: the moved value times 1 or 0 is added by
+// one multiply-add with a DPP operand, a third of the instructions (and the
+// same sums: the product is exact). The values' last writers may be the two
+// instructions before (a DPP operand needs two wait states).
+#define HTGS_SEG_FMAC(ctrl, v, take)                                                         \
+  _Pragma("unroll") for (int k_ = 0; k_ < kPartialFloats; k_ += 4)                           \
+    asm("s_nop 1\n\t"                                                                        \
+        "v_fmac_f32_dpp %0, %0, %4 " ctrl " row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"     \
+        "v_fmac_f32_dpp %1, %1, %4 " ctrl " row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"     \
+        "v_fmac_f32_dpp %2, %2, %4 " ctrl " row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"     \
+        "v_fmac_f32_dpp %3, %3, %4 " ctrl " row_mask:0xf bank_mask:0xf bound_ctrl:0"         \
+        : "+v"((v)[k_]), "+v"((v)[k_ + 1]), "+v"((v)[k_ + 2]), "+v"((v)[k_ + 3])             \
+        : "v"(take))
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ void seg_scan_step_finite(uint32_t seg, float *v) {
+  const uint32_t src = (uint32_t)__builtin_amdgcn_update_dpp((int)~seg, (int)seg, CTRL, ROW_MASK,
+                                                             0xf, false);
+  const float take = src == seg ? 1.f : 0.f;
+  if constexpr (CTRL == 0x111) HTGS_SEG_FMAC("row_shr:1", v, take);
+  if constexpr (CTRL == 0x112) HTGS_SEG_FMAC("row_shr:2", v, take);
+  if constexpr (CTRL == 0x114) HTGS_SEG_FMAC("row_shr:4", v, take);
+  if constexpr (CTRL == 0x118) HTGS_SEG_FMAC("row_shr:8", v, take);
+  if constexpr (CTRL == 0x142) HTGS_SEG_FMAC("row_bcast:15", v, take);
+  if constexpr (CTRL == 0x143) HTGS_SEG_FMAC("row_bcast:31", v, take);
+}
+#undef HTGS_SEG_FMAC
+
 // ws[k] = sh_k . gc for the NB basis functions of one Gaussian, reading the
 // coefficient row four basis functions (three 16-byte loads) at a time
 // where the row allows it.
@@ -1023,43 +1050,157 @@ __device__ __forceinline__ void sh_backward(const float *wsv, const double dir[3
 }
 
 
-// Each wave owns 64 consecutive Gaussians (one slot group: their instance
-// slots are one contiguous range, view by view). For each view the wave
-// walks that view's part of the range 64 slots at a time with the
-// segmented scan and adds each segment's sum into its owner's LDS column,
-// so the partials are read once, coalesced. A slot's owner is the last
-// Gaussian of the group whose first slot is at or before it (first slots
-// increase with the Gaussian): each owner marks its first slot in LDS and
-// a prefix maximum over the chunk fills the rest. Then every lane turns its
-// Gaussian's summed moments for the view into gradients of the Pluecker
-// coefficients (float64) and those into parameter gradients.
-template <int DEG, bool MV>
-__global__ void __launch_bounds__(256, MV ? 2 : 1) k_preprocess_bwd(GaussPtrs gp, GradPtrs gr, KCfg cfg,
-                                                         ViewSet vs, Ws w) {
-  constexpr int NB = (DEG + 1) * (DEG + 1);
+// Sums of one view's partials of a wave's 64 Gaussians, lane l's Gaussian
+// (first slot, cnt slots) into LDS column l of acc: the wave walks the view's
+// slots lo .. hi - 1 of the group, one contiguous range, 64 at a time with
+// the segmented scan and adds each segment's sum into its owner's column, so
+// the partials are read once, coalesced. A slot's owner is the last Gaussian
+// of the group whose first slot is at or before it (first slots increase
+// with the lane): each owner marks its first slot in LDS and a prefix
+// maximum over the chunk fills the rest. All 64 lanes.
+__device__ __forceinline__ void scan_partials(const float *__restrict__ partials, uint64_t lo,
+                                              uint64_t hi, uint32_t first, uint32_t cnt,
+                                              float (*acc)[64], uint32_t *mark, int lane) {
+#pragma unroll
+  for (int k = 0; k < kPartialFloats; ++k) acc[k][lane] = 0.f;
+  __builtin_amdgcn_wave_barrier();
+  // Partials of slot sl (zeros past the range).
+  auto load_partial = [&](uint64_t sl, float *pv) {
+    if (sl < hi) {
+      const float4 *P = reinterpret_cast<const float4 *>(partials + (int64_t)sl * kPartialFloats);
+#pragma unroll
+      for (int k = 0; k < kPartialFloats / 4; ++k) {
+        const float4 t = P[k];
+        pv[4 * k] = t.x; pv[4 * k + 1] = t.y; pv[4 * k + 2] = t.z; pv[4 * k + 3] = t.w;
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < kPartialFloats; ++k) pv[k] = 0.f;
+    }
+  };
+  // The next 64 slots are loaded while this chunk is scanned.
+  float nv[kPartialFloats];
+  load_partial(lo + lane, nv);
+  int carry = -1;   // owner of the slot before the chunk
+  for (uint64_t base = lo; base < hi; base += 64) {
+    const uint64_t sl = base + lane;
+    const bool valid = sl < hi;
+    float pv[kPartialFloats];
+#pragma unroll
+    for (int k = 0; k < kPartialFloats; ++k) pv[k] = nv[k];
+    if (base + 64 < hi) load_partial(base + 64 + lane, nv);
+    // owners: marks at first slots, then a prefix maximum
+    mark[lane] = 0u;
+    __builtin_amdgcn_wave_barrier();
+    if (cnt && (uint64_t)first >= base && (uint64_t)first < base + 64)
+      mark[first - base] = (uint32_t)lane + 1u;
+    __builtin_amdgcn_wave_barrier();
+    const int own = max((int)wave_incl_max(mark[lane]) - 1, carry);
+    carry = __builtin_amdgcn_readlane(own, 63);
+    const uint32_t seg = valid ? (uint32_t)own : 0xffffffffu;
+    // Inclusive segmented scan over the wave with DPP lane moves (no
+    // LDS): shifts by 1, 2, 4, 8 inside each row of 16 lanes, then the
+    // last lane of row 0 / row 2 into rows 1 / 3, then lane 31 into rows
+    // 2 and 3. Segments are runs of consecutive slots, so equal owners
+    // mean one run; the fixed tree makes the sums deterministic.
+    float z = 0.f;   // NaN if any value is infinite or NaN
+#pragma unroll
+    for (int k = 0; k < kPartialFloats; ++k) z = fmaf(pv[k], 0.f, z);
+    if (__ballot(z != 0.f) == 0ull) {
+      seg_scan_step_finite<0x111, 0xf>(seg, pv);   // row_shr:1
+      seg_scan_step_finite<0x112, 0xf>(seg, pv);   // row_shr:2
+      seg_scan_step_finite<0x114, 0xf>(seg, pv);   // row_shr:4
+      seg_scan_step_finite<0x118, 0xf>(seg, pv);   // row_shr:8
+      seg_scan_step_finite<0x142, 0xa>(seg, pv);   // row_bcast:15 into rows 1, 3
+      seg_scan_step_finite<0x143, 0xc>(seg, pv);   // row_bcast:31 into rows 2, 3
+    } else {
+      seg_scan_step<0x111, 0xf>(seg, pv);
+      seg_scan_step<0x112, 0xf>(seg, pv);
+      seg_scan_step<0x114, 0xf>(seg, pv);
+      seg_scan_step<0x118, 0xf>(seg, pv);
+      seg_scan_step<0x142, 0xa>(seg, pv);
+      seg_scan_step<0x143, 0xc>(seg, pv);
+    }
+    const uint32_t sn = __shfl_down(seg, 1, 64);
+    const bool end = valid && own >= 0 && (lane == 63 || sn != seg || sl + 1 == hi);
+    if (end) {
+#pragma unroll
+      for (int k = 0; k < kPartialFloats; ++k) acc[k][own] += pv[k];
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// Whether the forward left partials to sum (an overflowed one, reported by
+// the status word, did not: zero gradient).
+__device__ __forceinline__ bool partials_ok(const Ws &w) {
+  return *w.total <= (unsigned long long)w.capacity && !front_failed(w);
+}
+
+// Sorted blending: the sums of each Gaussian's partials, in place, to its
+// first slot. The instances were emitted in depth order, so a wave's group of
+// slots belongs to 64 Gaussians of that order, scattered in memory; with the
+// sums in place the chain rule runs in index order, where the parameters and
+// gradients lie side by side (720p, 1M Gaussians: 222 us for both launches,
+// 332 us when one launch did it all in depth order). In index order one
+// launch does both: the two take 271 us against 221 at 1080p, the summed
+// rows being a scattered write and read more.
+__global__ void __launch_bounds__(256) k_sum_partials(KCfg cfg, Ws w) {
   __shared__ float s_acc[4][kPartialFloats][64];
-  __shared__ int s_own[4][64];
+  __shared__ uint32_t s_mark[4][64];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t pos = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t pos0 = pos - lane;
-  if (pos0 >= cfg.n) return;  // uniform over the wave
-  const int nviews = MV ? vs.n : 1;
-  const unsigned long long I = *w.total;
-  // An overflowed forward (reported by the status word) leaves no usable
-  // partials: zero gradient.
-  const bool ok = I <= (unsigned long long)w.capacity && !front_failed(w);
-  // Sorted blending emitted the instances in the depth order of its
-  // Gaussians (position p holds Gaussian perm[p]), so a group of 64
-  // positions owns one contiguous slot range; otherwise positions are
-  // Gaussian indices. (Without usable partials the index order serves.)
-  const bool by_perm = w.perm != nullptr && ok;
+  if (pos0 >= cfg.n || !partials_ok(w)) return;  // uniform over the wave
   auto gauss_at = [&](int64_t p) -> int64_t {
-    if (!by_perm) return p;
     const uint32_t x = w.perm[p];
     return (int64_t)x < cfg.n ? (int64_t)x : p;
   };
   const bool live = pos < cfg.n;
   const int64_t g = live ? gauss_at(pos) : pos;
+  const uint64_t I = *w.total;
+  const uint64_t lo = w.tslots[gauss_at(pos0)].x;
+  const uint64_t hi = pos0 + 64 < cfg.n ? min((uint64_t)w.tslots[gauss_at(pos0 + 64)].x, I) : I;
+  if (lo >= hi) return;
+  const uint4 myd = live ? w.tslots[g] : make_uint4(0u, 0u, 0u, 0u);
+  const uint32_t cnt = live ? (uint32_t)tile_count(w.rects[g], tslot_mask(myd)) : 0u;
+  scan_partials(w.partials, lo, hi, myd.x, cnt, s_acc[wave], s_mark[wave], lane);
+  // (every row of the group has been read; four lanes per 64 bytes)
+  const uint32_t slot = cnt ? myd.x : 0xffffffffu;
+#pragma unroll
+  for (int it = 0; it < 4; ++it) {
+    const int r = it * 16 + (lane >> 2), p = (lane & 3) * 4;
+    const uint32_t sr = (uint32_t)__shfl((int)slot, r, 64);
+    if (sr != 0xffffffffu)
+      reinterpret_cast<float4 *>(w.partials)[(int64_t)sr * (kPartialFloats / 4) + (lane & 3)] =
+          make_float4(s_acc[wave][p][r], s_acc[wave][p + 1][r], s_acc[wave][p + 2][r],
+                      s_acc[wave][p + 3][r]);
+  }
+}
+
+// Each wave owns 64 consecutive Gaussians (one slot group). Bound by its
+// float64 chain rule and scan (VALU, three waves per SIMD) and by memory at
+// once (0.9 GB at 1080p and 1M Gaussians: 208 us, 221 with the scan in three
+// instructions per value and step; 8 views of 500k: 447 us, 539 before).
+// Four lanes adding up one Gaussian's rows one after another instead of the
+// scan took 264 us at 1080p. For each view the wave
+// sums their partials (scan_partials), or finds the sums in their first
+// slots (SUMMED), then every lane turns its Gaussian's summed moments into
+// gradients of the Pluecker coefficients (float64) and those into parameter
+// gradients.
+template <int DEG, bool MV, bool SUMMED>
+__global__ void __launch_bounds__(256, MV ? 2 : 1) k_preprocess_bwd(GaussPtrs gp, GradPtrs gr, KCfg cfg,
+                                                         ViewSet vs, Ws w) {
+  constexpr int NB = (DEG + 1) * (DEG + 1);
+  __shared__ float s_acc[SUMMED ? 1 : 4][kPartialFloats][64];
+  __shared__ uint32_t s_mark[SUMMED ? 1 : 4][64];
+  const int wave = SUMMED ? 0 : threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t pos0 = g - lane;
+  if (pos0 >= cfg.n) return;  // uniform over the wave
+  const int nviews = MV ? vs.n : 1;
+  const bool ok = partials_ok(w);
+  const bool live = g < cfg.n;
   uint32_t total = 0;
   if (live && ok)
     for (int v = 0; v < nviews; ++v)
@@ -1086,84 +1227,35 @@ __global__ void __launch_bounds__(256, MV ? 2 : 1) k_preprocess_bwd(GaussPtrs gp
   const float *shrow = gp.sh + g * NB * 3;
 
   if (ok && __ballot(total != 0) != 0ull) {
-    const int64_t gfirst = gauss_at(pos0);
-    const uint64_t group_end =
-        (pos0 + 64 < cfg.n) ? (uint64_t)w.tslots[gauss_at(pos0 + 64)].x : (uint64_t)I;
+    const uint64_t I = *w.total;
+    const uint64_t group_end = (pos0 + 64 < cfg.n) ? (uint64_t)w.tslots[pos0 + 64].x : I;
     for (int v = 0; v < nviews; ++v) {
-      const uint64_t lo = w.tslots[(int64_t)v * cfg.n + gfirst].x;
-      const uint64_t hi = min((v + 1 < nviews) ? (uint64_t)w.tslots[(int64_t)(v + 1) * cfg.n + gfirst].x
-                                               : group_end, (uint64_t)I);
-      if (lo >= hi) continue;  // no instance of this group in view v
-#pragma unroll
-      for (int k = 0; k < kPartialFloats; ++k) s_acc[wave][k][lane] = 0.f;
       // this lane's Gaussian in view v: first slot, instance count
       const uint4 myd = live ? w.tslots[(int64_t)v * cfg.n + g] : make_uint4(0u, 0u, 0u, 0u);
       const uint32_t mycnt =
           (live && total) ? (uint32_t)tile_count(w.rects[(int64_t)v * cfg.n + g], tslot_mask(myd)) : 0u;
-      __builtin_amdgcn_wave_barrier();
-      // Partials of slot sl (zeros past the range).
-      auto load_partial = [&](uint64_t sl, float *pv) {
-        if (sl < hi) {
-          const float4 *P = reinterpret_cast<const float4 *>(w.partials + (int64_t)sl * kPartialFloats);
+      if constexpr (!SUMMED) {
+        const uint64_t lo = w.tslots[(int64_t)v * cfg.n + pos0].x;
+        const uint64_t hi = min((v + 1 < nviews) ? (uint64_t)w.tslots[(int64_t)(v + 1) * cfg.n + pos0].x
+                                                 : group_end, I);
+        if (lo >= hi) continue;  // no instance of this group in view v
+        scan_partials(w.partials, lo, hi, myd.x, mycnt, s_acc[wave], s_mark[wave], lane);
+        __builtin_amdgcn_wave_barrier();
+      }
+      if (mycnt) {
+        float acc[kPartialFloats];
+        if constexpr (SUMMED) {
+          const float4 *P =
+              reinterpret_cast<const float4 *>(w.partials) + (int64_t)myd.x * (kPartialFloats / 4);
 #pragma unroll
           for (int k = 0; k < kPartialFloats / 4; ++k) {
             const float4 t = P[k];
-            pv[4 * k] = t.x; pv[4 * k + 1] = t.y; pv[4 * k + 2] = t.z; pv[4 * k + 3] = t.w;
+            acc[4 * k] = t.x; acc[4 * k + 1] = t.y; acc[4 * k + 2] = t.z; acc[4 * k + 3] = t.w;
           }
         } else {
 #pragma unroll
-          for (int k = 0; k < kPartialFloats; ++k) pv[k] = 0.f;
+          for (int k = 0; k < kPartialFloats; ++k) acc[k] = s_acc[wave][k][lane];
         }
-      };
-      // The next 64 slots are loaded while this chunk is scanned.
-      float nv[kPartialFloats];
-      load_partial(lo + lane, nv);
-      int carry = -1;   // owner of the slot before the chunk
-      for (uint64_t base = lo; base < hi; base += 64) {
-        const uint64_t sl = base + lane;
-        const bool valid = sl < hi;
-        float pv[kPartialFloats];
-#pragma unroll
-        for (int k = 0; k < kPartialFloats; ++k) pv[k] = nv[k];
-        if (base + 64 < hi) load_partial(base + 64 + lane, nv);
-        // owners: marks at first slots, then a prefix maximum
-        s_own[wave][lane] = -1;
-        __builtin_amdgcn_wave_barrier();
-        if (mycnt && (uint64_t)myd.x >= base && (uint64_t)myd.x < base + 64)
-          s_own[wave][myd.x - base] = lane;
-        __builtin_amdgcn_wave_barrier();
-        int own = max(s_own[wave][lane], carry);
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const int y = __shfl_up(own, off, 64);
-          if (lane >= off) own = max(own, y);
-        }
-        carry = __shfl(own, 63, 64);
-        const uint32_t seg = valid ? (uint32_t)own : 0xffffffffu;
-        // Inclusive segmented scan over the wave with DPP lane moves (no
-        // LDS): shifts by 1, 2, 4, 8 inside each row of 16 lanes, then the
-        // last lane of row 0 / row 2 into rows 1 / 3, then lane 31 into rows
-        // 2 and 3. Segments are runs of consecutive slots, so equal owners
-        // mean one run; the fixed tree makes the sums deterministic.
-        seg_scan_step<0x111, 0xf>(seg, pv);   // row_shr:1
-        seg_scan_step<0x112, 0xf>(seg, pv);   // row_shr:2
-        seg_scan_step<0x114, 0xf>(seg, pv);   // row_shr:4
-        seg_scan_step<0x118, 0xf>(seg, pv);   // row_shr:8
-        seg_scan_step<0x142, 0xa>(seg, pv);   // row_bcast:15 into rows 1, 3
-        seg_scan_step<0x143, 0xc>(seg, pv);   // row_bcast:31 into rows 2, 3
-        const uint32_t sn = __shfl_down(seg, 1, 64);
-        const bool end = valid && own >= 0 && (lane == 63 || sn != seg || sl + 1 == hi);
-        if (end) {
-#pragma unroll
-          for (int k = 0; k < kPartialFloats; ++k) s_acc[wave][k][own] += pv[k];
-        }
-        __builtin_amdgcn_wave_barrier();
-      }
-      __builtin_amdgcn_wave_barrier();
-      if (mycnt) {
-        float acc[kPartialFloats];
-#pragma unroll
-        for (int k = 0; k < kPartialFloats; ++k) acc[k] = s_acc[wave][k][lane];
         const ViewParams &V = vs.v[v];
         // Pluecker coefficients in camera coordinates (d = D + u Du + v Dv,
         // u = (x + 1/2 - cx) / fx) and, from the summed moments about the
@@ -1398,15 +1490,19 @@ hipError_t launch_preprocess_bwd(const GaussPtrs &gp, const GradPtrs &gr, const 
                                  const ViewSet &vs, const Ws &w, hipStream_t s) {
   if (cfg.n == 0) return hipSuccess;
   const int blocks = (int)((cfg.n + 255) / 256);
+  const bool summed = w.perm && w.capacity > 0;
+  if (summed) {
+    hipLaunchKernelGGL(k_sum_partials, dim3(blocks), dim3(256), 0, s, cfg, w);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   switch (cfg.sh_degree) {
 #define HTGS_PREB(D)                                                                       \
   do {                                                                                     \
-    if (vs.n > 1)                                                                          \
-      hipLaunchKernelGGL((k_preprocess_bwd<D, true>), dim3(blocks), dim3(256), 0, s, gp, gr, \
-                         cfg, vs, w);                                                      \
-    else                                                                                   \
-      hipLaunchKernelGGL((k_preprocess_bwd<D, false>), dim3(blocks), dim3(256), 0, s, gp, gr, \
-                         cfg, vs, w);                                                      \
+    auto *k = vs.n > 1 ? k_preprocess_bwd<D, true, false>                                  \
+                       : (summed ? k_preprocess_bwd<D, false, true>                        \
+                                 : k_preprocess_bwd<D, false, false>);                     \
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, s, gp, gr, cfg, vs, w);              \
   } while (0)
     case 0: HTGS_PREB(0); break;
     case 1: HTGS_PREB(1); break;
