@@ -13,6 +13,8 @@ hipError_t launch_fill_zero(void *p, int64_t bytes, hipStream_t s);
 hipError_t launch_opacity_decay(float *x, int64_t n, double lambda, hipStream_t s);
 hipError_t launch_preprocess(const GaussPtrs &gp, const KCfg &cfg, const ViewSet &vs, const Ws &w,
                              hipStream_t s);
+hipError_t launch_count(const GaussPtrs &gp, const KCfg &cfg, const ViewSet &vs, const Ws &w,
+                        hipStream_t s);
 hipError_t launch_preprocess_bwd(const GaussPtrs &gp, const GradPtrs &gr, const KCfg &cfg,
                                  const ViewSet &vs, const Ws &w, hipStream_t s);
 hipError_t launch_sort_passes(const Ws &w, hipStream_t s);
@@ -361,7 +363,7 @@ struct StageTimer {
 };
 
 int run_front(const htgs_gaussians *g, const ViewSet &vs, const htgs_config *cfg, const Layout &L,
-              void *ws, hipStream_t s, bool sort, bool timed = true) {
+              void *ws, hipStream_t s, bool timed = true) {
   const Ws w = make_ws(ws, L);
   {
     StageTimer t(HTGS_STAGE_FILL, s, 1, timed);
@@ -375,11 +377,11 @@ int run_front(const htgs_gaussians *g, const ViewSet &vs, const htgs_config *cfg
     StageTimer t(HTGS_STAGE_PREPROCESS, s, 1, timed);
     HIP_TRY(launch_preprocess(make_gp(g), make_kcfg(g, cfg, vs.total_tiles), vs, w, s));
   }
-  if (sort && L.capacity > 0) {
+  if (L.capacity > 0) {
     StageTimer t(HTGS_STAGE_SORT, s, 3 * L.passes, timed);
     HIP_TRY(launch_sort_passes(w, s));
   }
-  if (sort && L.capacity > 0) {
+  if (L.capacity > 0) {
     StageTimer t(HTGS_STAGE_RANGES, s, 1, timed);
     HIP_TRY(launch_ranges(w, vs.total_tiles, s));
     if (cfg->flags & HTGS_FLAG_COST_ORDER) HIP_TRY(launch_tile_order(w, vs.total_tiles, s));
@@ -404,7 +406,7 @@ int forward_impl(const htgs_gaussians *g, const htgs_camera *cams, int32_t n_vie
   const Layout L = make_layout(g->n, n_views, tiles, cap, partials, srt);
   const ViewSet vs = make_views(cams, n_views, cfg, out_rgb, nullptr);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if ((e = run_front(g, vs, cfg, L, ws, s, true, partials))) return e;
+  if ((e = run_front(g, vs, cfg, L, ws, s, partials))) return e;
   const Ws w = make_ws(ws, L);
   StageTimer t(HTGS_STAGE_RASTER_FWD, s, 1, partials);
   HIP_TRY(launch_raster_fwd(w, vs, make_kcfg(g, cfg, tiles), static_cast<float *>(state),
@@ -558,11 +560,18 @@ int htgs_count_instances(const htgs_gaussians *g, const htgs_camera *cams, int32
   const int64_t tiles = total_tiles_of(cams, n_views, cfg);
   const int64_t cap = capacity_for(g->n, n_views, tiles, ws_bytes, true, sorted_of(cfg));
   if (cap < 0) return HTGS_E_WORKSPACE;
-  // Count with capacity 0: nothing is emitted, the scan still runs.
+  // Only the totals and their scan, with capacity 0.
   const Layout L0 = make_layout(g->n, n_views, tiles, 0, true, sorted_of(cfg));
   const ViewSet vs = make_views(cams, n_views, cfg, nullptr, nullptr);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if ((e = run_front(g, vs, cfg, L0, ws, s, false))) return e;
+  {
+    StageTimer t(HTGS_STAGE_FILL, s);
+    HIP_TRY(launch_fill_zero(ws, L0.pp_total, s));
+  }
+  {
+    StageTimer t(HTGS_STAGE_PREPROCESS, s);
+    HIP_TRY(launch_count(make_gp(g), make_kcfg(g, cfg, tiles), vs, make_ws(ws, L0), s));
+  }
   unsigned long long total = 0;
   HIP_TRY(hipMemcpyAsync(&total, static_cast<char *>(ws) + L0.total, sizeof(total),
                          hipMemcpyDeviceToHost, s));
