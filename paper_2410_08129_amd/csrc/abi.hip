@@ -641,18 +641,22 @@ int htgs_read_status(const void *ws, int64_t ws_bytes, uint32_t *flags_out,
   const Layout L = make_layout(0, 1, 1, 0);
   if (!ws || !flags_out || ws_bytes < L.pp_total) return HTGS_E_INVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  // one copy for the flags and the instance count: each costs the host about
+  // 10 us
+  char head[4 * kStatusWords + 8];
   uint32_t flags = 0;
   unsigned long long total = 0;
   int64_t fwd = 0, bwd = 0;
-  HIP_TRY(hipMemcpyAsync(&flags, static_cast<const char *>(ws) + L.status, 4,
-                         hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(&total, static_cast<const char *>(ws) + L.total, 8,
+  if (L.total + 8 - L.status > (int64_t)sizeof(head)) return HTGS_E_INVAL;
+  HIP_TRY(hipMemcpyAsync(head, static_cast<const char *>(ws) + L.status, L.total + 8 - L.status,
                          hipMemcpyDeviceToHost, s));
   if (fragments_out) {
     int e = read_counters(ws, L, &fwd, &bwd, s);
     if (e) return e;
   }
   HIP_TRY(hipStreamSynchronize(s));
+  memcpy(&flags, head, 4);
+  memcpy(&total, head + (L.total - L.status), 8);
   *flags_out = flags & kStatusPublic;
   if (instances_out) *instances_out = (int64_t)total;
   if (fragments_out) *fragments_out = fwd;
