@@ -348,13 +348,45 @@ struct FwdLds {
     uint2 fill[kWaves][kParts * NBATCH / 4];
   };
   uint32_t mask[kWaves > 1 ? NBATCH : 1];
+  uint32_t reach[kWaves > 1 ? NBATCH : 1];
 };
+
+// What a wave knows about the staged batch as a whole.
+struct BatchInfo {
+  int nlist;     // length of its longest list, rounded up to an even number
+  float reach;   // no fragment lies further in front of its splat's mean
+};
+
+// Largest of the wave's values. All 64 lanes.
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+#define HTGS_MAX_DPP(CTRL) \
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true))
+  HTGS_MAX_DPP(0x111);   // row_shr:1, 2, 4, 8
+  HTGS_MAX_DPP(0x112);
+  HTGS_MAX_DPP(0x114);
+  HTGS_MAX_DPP(0x118);
+  HTGS_MAX_DPP(0x142);   // row_bcast:15, 31
+  HTGS_MAX_DPP(0x143);
+#undef HTGS_MAX_DPP
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+
+// How far in front of its splat's mean a fragment's depth can lie (bits of a
+// float that is not negative, or of a NaN): z = muz + R3 . (d x m) / |d|^2
+// with |m| <= sqrt(rho_c) |d|, so |R3| sqrt(rho_c), and a quarter more, with
+// 2^-20 of the depth, for the rounding of z.
+__device__ __forceinline__ uint32_t depth_reach(const float *rec) {
+  const float r2 = dot_f(rec + R_R3, rec + R_R3);
+  return __float_as_uint(
+      fmaf(1.25f, __builtin_amdgcn_sqrtf(r2 * rec[R_RC]), 9.6e-7f * fabsf(rec[R_MUZ]))) &
+         0x7fffffffu;
+}
 
 // Stages one splat; returns the parts it can reach.
 template <int TW, int TH, int NBATCH>
 __device__ __forceinline__ uint32_t stage_splat(FwdLds<TW, TH, NBATCH> &L, int r,
                                                 const float *__restrict__ recs, uint32_t gid,
-                                                int px0, int py0) {
+                                                int px0, int py0, uint32_t *reach) {
   float rec[kRecFloats];
   load_record(recs, gid, rec);
   float st[F_FLOATS];
@@ -363,6 +395,7 @@ __device__ __forceinline__ uint32_t stage_splat(FwdLds<TW, TH, NBATCH> &L, int r
   for (int k = 0; k < F_FLOATS / 4; ++k)
     L.stage[r * (F_FLOATS / 4) + k] =
         make_float4(st[4 * k], st[4 * k + 1], st[4 * k + 2], st[4 * k + 3]);
+  *reach = depth_reach(rec);
   return part_mask<TW, TH>(st) &
          rect_block_mask<TW, TH>(__float_as_uint(rec[R_BB0]), __float_as_uint(rec[R_BB1]), px0, py0);
 }
@@ -384,15 +417,16 @@ __device__ __forceinline__ void extend_lists(uint16_t (*list)[NBATCH], int j, ui
 }
 
 // Stages up to NBATCH splats of a tile's list (cnt of them from vals on) and
-// builds this wave's lists; returns the longest one's length, an even number
-// (the lists are padded with the zero row). All threads of the workgroup.
+// builds this wave's lists (padded with the zero row to the longest one's
+// even length). All threads of the workgroup.
 template <int TW, int TH, int NBATCH>
-__device__ __forceinline__ int stage_batch(FwdLds<TW, TH, NBATCH> &L,
-                                           const float *__restrict__ recs,
-                                           const uint32_t *__restrict__ vals, int cnt, int px0,
-                                           int py0, int wave, int lane) {
+__device__ __forceinline__ BatchInfo stage_batch(FwdLds<TW, TH, NBATCH> &L,
+                                                 const float *__restrict__ recs,
+                                                 const uint32_t *__restrict__ vals, int cnt,
+                                                 int px0, int py0, int wave, int lane) {
   constexpr int NT = TW * TH;
   int n[kParts];
+  uint32_t reach = 0u;
 #pragma unroll
   for (int p = 0; p < kParts; ++p) n[p] = 0;
   constexpr uint32_t kZeroRow = (uint32_t)(NBATCH * kStageBytes);
@@ -406,19 +440,25 @@ __device__ __forceinline__ int stage_batch(FwdLds<TW, TH, NBATCH> &L,
 #pragma unroll
     for (int r0 = 0; r0 < NBATCH; r0 += 64) {
       const int r = r0 + lane;
-      uint32_t m = 0u;
-      if (r < cnt) m = stage_splat(L, r, recs, vals[r], px0, py0);
+      uint32_t m = 0u, e = 0u;
+      if (r < cnt) m = stage_splat(L, r, recs, vals[r], px0, py0, &e);
+      reach = max(reach, e);
       extend_lists<NBATCH>(L.list[0], r, m, n);
     }
     __syncthreads();
   } else {
     static_assert(NBATCH == NT, "one record per thread");
     const int r = wave * 64 + lane;
-    if (r < cnt) L.mask[r] = stage_splat(L, r, recs, vals[r], px0, py0);
+    if (r < cnt) {
+      uint32_t e;
+      L.mask[r] = stage_splat(L, r, recs, vals[r], px0, py0, &e);
+      L.reach[r] = e;
+    }
     __syncthreads();
     for (int j0 = 0; j0 < cnt; j0 += 64) {
       const int j = j0 + lane;
       const uint32_t m = j < cnt ? L.mask[j] >> (kParts * wave) : 0u;
+      reach = max(reach, j < cnt ? L.reach[j] : 0u);
       extend_lists<NBATCH>(L.list[wave], j, m, n);
     }
     __builtin_amdgcn_wave_barrier();
@@ -426,7 +466,7 @@ __device__ __forceinline__ int stage_batch(FwdLds<TW, TH, NBATCH> &L,
   int longest = 0;
 #pragma unroll
   for (int p = 0; p < kParts; ++p) longest = max(longest, n[p]);
-  return (longest + 1) & ~1;
+  return {(longest + 1) & ~1, __uint_as_float(wave_max(reach))};
 }
 
 // Core keys: depth in the high word, list position and alpha slot in the
@@ -535,8 +575,13 @@ __device__ __forceinline__ void fwd_tile(const TileInfo &ti, const Ws &w, const 
   for (uint32_t base = rg.x; base < rg.y; base += NBATCH) {
     const int cnt = (int)min((uint32_t)NBATCH, rg.y - base);
     __syncthreads();
-    const int nlist = stage_batch(L, recs, vals + base, cnt, px0, py0, wave, lane);
+    const BatchInfo batch = stage_batch(L, recs, vals + base, cnt, px0, py0, wave, lane);
     if (!inside) continue;
+    // A splat whose mean lies at this depth or further back has no fragment
+    // in front of the last core entry, and its depth is not evaluated (two
+    // thirds of the steps of a wave with 786 splats per tile and K = 16, half
+    // of them with 205 and K = 8: 7.01 -> 6.70 ms and 425 -> 411 us).
+    float far = __uint_as_float(key_hi(key[KMAX - 1])) + batch.reach;
     const char *rows = reinterpret_cast<const char *>(L.stage);
     // (opaque: otherwise each component is read by itself where it is used)
     auto row4 = [&](uint32_t off, int k) -> float4v {
@@ -568,7 +613,8 @@ __device__ __forceinline__ void fwd_tile(const TileInfo &ti, const Ws &w, const 
         S2 = fmaf(alpha, f4.x, S2);
         P *= 1.f - alpha;
       }
-      if (alpha >= tau_core) {
+      // (also where a reach is not finite)
+      if (!(f4.y >= far) && alpha >= tau_core) {
         const float4v f5 = row4(off, F_QZ / 4);   // qz0..qz3
         const float qz[6] = {f5.x, f5.y, f5.z, f5.w, f4.z, f4.w};
         const float z = fmaf(eval_q(qz, u), inv, f4.y);
@@ -578,6 +624,7 @@ __device__ __forceinline__ void fwd_tile(const TileInfo &ti, const Ws &w, const 
           const uint32_t pos = (base - rg.x) + ((off * 683u) >> 16);
           my_alpha[slot * 64u] = alpha;
           core_insert<KMAX>(key, core_key(__float_as_uint(z), (pos << SB) | slot));
+          far = __uint_as_float(key_hi(key[KMAX - 1])) + batch.reach;
         }
       }
     };
@@ -585,7 +632,7 @@ __device__ __forceinline__ void fwd_tile(const TileInfo &ti, const Ws &w, const 
     // (the last look-up lies past the list, inside L, and is not used).
     const uint32_t *list = reinterpret_cast<const uint32_t *>(L.list[wave][lane / kPartLanes]);
     uint32_t next = list[0];
-    for (int q = 0; q < nlist; q += 2) {
+    for (int q = 0; q < batch.nlist; q += 2) {
       const uint32_t o = next;
       next = list[q / 2 + 1];
       step(o & 0xffffu);
@@ -734,7 +781,7 @@ __device__ __forceinline__ void fwd_tile_sorted(const TileInfo &ti, const Ws &w,
     // (also the barrier before the stage is overwritten)
     if (__syncthreads_and(done)) break;
     const int cnt = (int)min((uint32_t)NT, rg.y - base);
-    const int nlist = stage_batch(L, recs, vals + base, cnt, px0, py0, wave, lane);
+    const int nlist = stage_batch(L, recs, vals + base, cnt, px0, py0, wave, lane).nlist;
     if (done) continue;
     const char *rows = reinterpret_cast<const char *>(L.stage);
     const uint16_t *list = L.list[wave][lane / kPartLanes];
