@@ -351,6 +351,21 @@ struct FwdLds {
   uint32_t reach[kWaves > 1 ? NBATCH : 1];
 };
 
+// A staged row in registers (opaque: otherwise each component is read by
+// itself where it is used).
+struct StagedRow {
+  float4v q[F_FLOATS / 4];
+};
+__device__ __forceinline__ StagedRow read_row(const char *p) {
+  StagedRow row;
+#pragma unroll
+  for (int k = 0; k < F_FLOATS / 4; ++k) {
+    row.q[k] = *reinterpret_cast<const float4v *>(p + 16 * k);
+    asm("" : "+v"(row.q[k]));
+  }
+  return row;
+}
+
 // What a wave knows about the staged batch as a whole.
 struct BatchInfo {
   int nlist;     // length of its longest list, rounded up to an even number
@@ -583,27 +598,21 @@ __device__ __forceinline__ void fwd_tile(const TileInfo &ti, const Ws &w, const 
     // of them with 205 and K = 8: 7.01 -> 6.70 ms and 425 -> 411 us).
     float far = __uint_as_float(key_hi(key[KMAX - 1])) + batch.reach;
     const char *rows = reinterpret_cast<const char *>(L.stage);
-    // (opaque: otherwise each component is read by itself where it is used)
-    auto row4 = [&](uint32_t off, int k) -> float4v {
-      float4v t = *reinterpret_cast<const float4v *>(rows + off + 16 * k);
-      asm("" : "+v"(t));
-      return t;
-    };
-    auto step = [&](uint32_t off) {
+    auto step = [&](uint32_t off, const StagedRow &row) {
       float e[12];
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
-        const float4v t = *reinterpret_cast<const float4v *>(rows + off + 16 * k);
+        const float4v t = row.q[k];
         e[4 * k] = t.x; e[4 * k + 1] = t.y; e[4 * k + 2] = t.z; e[4 * k + 3] = t.w;
       }
-      const float4v f3 = row4(off, F_RC / 4);   // rho_c, o, r, g
+      const float4v f3 = row.q[F_RC / 4];   // rho_c, o, r, g
+      const float4v f4 = row.q[F_B / 4];    // b, muz, qz4, qz5
       const float dd = eval_dd(e + F_QD, u);
       const float mm = eval_mm(e + F_QM, u);
       if (!is_fragment(dd, mm, f3.x)) return;
       ++nfrag;
       const float inv = rcp_fast(dd);
       const float alpha = frag_alpha(f3.y, mm, inv, amax);
-      const float4v f4 = row4(off, F_B / 4);   // b, muz, qz4, qz5
       int nt = no_tail;
       asm volatile("" : "+s"(nt));   // (a scalar test here, not a saved lane mask)
       if (nt == 0) {
@@ -615,7 +624,7 @@ __device__ __forceinline__ void fwd_tile(const TileInfo &ti, const Ws &w, const 
       }
       // (also where a reach is not finite)
       if (!(f4.y >= far) && alpha >= tau_core) {
-        const float4v f5 = row4(off, F_QZ / 4);   // qz0..qz3
+        const float4v f5 = row.q[F_QZ / 4];   // qz0..qz3
         const float qz[6] = {f5.x, f5.y, f5.z, f5.w, f4.z, f4.w};
         const float z = fmaf(eval_q(qz, u), inv, f4.y);
         if (z < __uint_as_float(key_hi(key[KMAX - 1]))) {
@@ -628,15 +637,19 @@ __device__ __forceinline__ void fwd_tile(const TileInfo &ti, const Ws &w, const 
         }
       }
     };
-    // Two splats per round; the next round's rows are looked up meanwhile
-    // (the last look-up lies past the list, inside L, and is not used).
+    // Two splats per round, both rows read whole before the first is used (a
+    // read where its values are needed leaves the wave waiting up to six
+    // times per round: 411 against 395 us for the launch at 1080p with K = 8);
+    // the next round's rows are looked up meanwhile (the last look-up lies
+    // past the list, inside L, and is not used).
     const uint32_t *list = reinterpret_cast<const uint32_t *>(L.list[wave][lane / kPartLanes]);
     uint32_t next = list[0];
     for (int q = 0; q < batch.nlist; q += 2) {
       const uint32_t o = next;
       next = list[q / 2 + 1];
-      step(o & 0xffffu);
-      step(o >> 16);
+      const StagedRow r0 = read_row(rows + (o & 0xffffu)), r1 = read_row(rows + (o >> 16));
+      step(o & 0xffffu, r0);
+      step(o >> 16, r1);
     }
   }
   static_assert(kStageBytes == 96 && NBATCH <= 256, "row numbers from byte offsets");
@@ -784,34 +797,38 @@ __device__ __forceinline__ void fwd_tile_sorted(const TileInfo &ti, const Ws &w,
     const int nlist = stage_batch(L, recs, vals + base, cnt, px0, py0, wave, lane).nlist;
     if (done) continue;
     const char *rows = reinterpret_cast<const char *>(L.stage);
-    const uint16_t *list = L.list[wave][lane / kPartLanes];
-    for (int q = 0; q < nlist; ++q) {
-      const uint32_t off = list[q];
+    auto step = [&](uint32_t off, const StagedRow &row) {
       float e[4 * F_TEST4];
 #pragma unroll
       for (int k = 0; k < F_TEST4; ++k) {
-        const float4 t = *reinterpret_cast<const float4 *>(rows + off + 16 * k);
+        const float4v t = row.q[k];
         e[4 * k] = t.x; e[4 * k + 1] = t.y; e[4 * k + 2] = t.z; e[4 * k + 3] = t.w;
       }
       const float dd = eval_dd(e + F_QD, u);
       const float mm = eval_mm(e + F_QM, u);
-      if (!is_fragment(dd, mm, e[F_RC])) continue;
+      if (!is_fragment(dd, mm, e[F_RC])) return;
       const float alpha = frag_alpha(e[F_O], mm, rcp_fast(dd), amax);
       const float tn = T * (1.f - alpha);
       const int pos = (int)((base - rg.x) + ((off * 683u) >> 16));
       if (tn < tau_T) {
         done = true;
         stop_pos = pos;
-        break;
+        return;
       }
-      const float bl = *reinterpret_cast<const float *>(rows + off + 4 * F_B);
       const float wgt = alpha * T;
       C0 = fmaf(wgt, e[F_R], C0);
       C1 = fmaf(wgt, e[F_G], C1);
-      C2 = fmaf(wgt, bl, C2);
+      C2 = fmaf(wgt, row.q[F_B / 4].x, C2);
       T = tn;
       ++nb;
       end_pos = pos + 1;
+    };
+    const uint32_t *list = reinterpret_cast<const uint32_t *>(L.list[wave][lane / kPartLanes]);
+    for (int q = 0; q < nlist && !done; q += 2) {
+      const uint32_t o = list[q / 2];
+      const StagedRow r0 = read_row(rows + (o & 0xffffu)), r1 = read_row(rows + (o >> 16));
+      step(o & 0xffffu, r0);
+      if (!done) step(o >> 16, r1);
     }
   }
   add_fragments(w, (uint32_t)nb, lane);
