@@ -12,9 +12,9 @@ namespace htgs {
 hipError_t launch_fill_zero(void *p, int64_t bytes, hipStream_t s);
 hipError_t launch_opacity_decay(float *x, int64_t n, double lambda, hipStream_t s);
 hipError_t launch_preprocess(const GaussPtrs &gp, const KCfg &cfg, const ViewSet &vs, const Ws &w,
-                             hipStream_t s);
+                             const Clear &clr, hipStream_t s);
 hipError_t launch_count(const GaussPtrs &gp, const KCfg &cfg, const ViewSet &vs, const Ws &w,
-                        hipStream_t s);
+                        const Clear &clr, hipStream_t s);
 hipError_t launch_preprocess_bwd(const GaussPtrs &gp, const GradPtrs &gr, const KCfg &cfg,
                                  const ViewSet &vs, const Ws &w, hipStream_t s);
 hipError_t launch_sort_passes(const Ws &w, hipStream_t s);
@@ -111,6 +111,8 @@ int64_t capacity_for(int64_t n, int n_views, int64_t total_tiles, int64_t ws_byt
   return lo;
 }
 
+bool few_chunks(int64_t capacity) { return capacity <= (int64_t)kFewChunks * kSortChunk; }
+
 Ws make_ws(void *base, const Layout &L) {
   char *b = static_cast<char *>(base);
   Ws w{};
@@ -151,6 +153,7 @@ Ws make_ws(void *base, const Layout &L) {
   w.passes = L.passes;
   w.digit_bits = L.digit_bits;
   w.key16 = L.key16;
+  w.few_chunks = few_chunks(L.capacity) ? 1 : 0;
   w.final_buf = L.passes & 1;
   return w;
 }
@@ -362,12 +365,31 @@ struct StageTimer {
   }
 };
 
+// What has to be zero before the preprocess' own outputs are read (count: for
+// the instance count alone).
+Clear make_clear(void *ws, const Layout &L, bool count) {
+  char *b = static_cast<char *>(ws);
+  const int64_t second = few_chunks(L.capacity) ? L.ranges : L.hist;
+  return {{reinterpret_cast<uint4 *>(b), reinterpret_cast<uint4 *>(b + second)},
+          {(uint32_t)(L.pp_total / 16), count ? 0u : (uint32_t)((L.zero_end - second) / 16)}};
+}
+
+// Whether the preprocess launch clears, which saves the launch of a fill (6 us
+// of a frame): not with a depth sort ahead of it, which needs its histograms
+// zero, nor where its threads would have to store more than 256 bytes each.
+bool preprocess_clears(int64_t n, const Clear &c) {
+  const int64_t threads = (n + kPreThreads - 1) / kPreThreads * kPreThreads;
+  return (int64_t)c.n[0] + c.n[1] <= 16 * threads;
+}
+
 int run_front(const htgs_gaussians *g, const ViewSet &vs, const htgs_config *cfg, const Layout &L,
               void *ws, hipStream_t s, bool timed = true) {
   const Ws w = make_ws(ws, L);
-  {
+  Clear clr = make_clear(ws, L, false);
+  if (L.sorted || !preprocess_clears(g->n, clr)) {
     StageTimer t(HTGS_STAGE_FILL, s, 1, timed);
     HIP_TRY(launch_fill_zero(ws, L.zero_end, s));
+    clr.n[0] = clr.n[1] = 0u;
   }
   if (L.sorted) {
     StageTimer t(HTGS_STAGE_DEPTH_SORT, s, 13, timed);
@@ -375,7 +397,8 @@ int run_front(const htgs_gaussians *g, const ViewSet &vs, const htgs_config *cfg
   }
   {
     StageTimer t(HTGS_STAGE_PREPROCESS, s, 1, timed);
-    HIP_TRY(launch_preprocess(make_gp(g), make_kcfg(g, cfg, vs.total_tiles), vs, w, s));
+    HIP_TRY(launch_preprocess(make_gp(g), make_kcfg(g, cfg, vs.total_tiles), vs, w,
+                              clr, s));
   }
   if (L.capacity > 0) {
     StageTimer t(HTGS_STAGE_SORT, s, 3 * L.passes, timed);
@@ -564,13 +587,15 @@ int htgs_count_instances(const htgs_gaussians *g, const htgs_camera *cams, int32
   const Layout L0 = make_layout(g->n, n_views, tiles, 0, true, sorted_of(cfg));
   const ViewSet vs = make_views(cams, n_views, cfg, nullptr, nullptr);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  {
+  Clear clr = make_clear(ws, L0, true);
+  if (!preprocess_clears(g->n, clr)) {
     StageTimer t(HTGS_STAGE_FILL, s);
     HIP_TRY(launch_fill_zero(ws, L0.pp_total, s));
+    clr.n[0] = 0u;
   }
   {
     StageTimer t(HTGS_STAGE_PREPROCESS, s);
-    HIP_TRY(launch_count(make_gp(g), make_kcfg(g, cfg, tiles), vs, make_ws(ws, L0), s));
+    HIP_TRY(launch_count(make_gp(g), make_kcfg(g, cfg, tiles), vs, make_ws(ws, L0), clr, s));
   }
   unsigned long long total = 0;
   HIP_TRY(hipMemcpyAsync(&total, static_cast<char *>(ws) + L0.total, sizeof(total),

@@ -12,6 +12,11 @@ constexpr int kPartialFloats = 16;  // per-instance backward partials (64 bytes)
 constexpr int kSortThreads = 256;
 constexpr int kSortItems = 16;
 constexpr int kSortChunk = kSortThreads * kSortItems;
+// Up to this many chunks of room, the scatter reads the digits' rows of chunk
+// counts whole (256 bytes each) and adds them up, and a pass takes two launches
+// instead of three (about 5 us each). Past one line per digit the rows'
+// reads cost more than the launch.
+constexpr int kFewChunks = 64;
 constexpr int kPreThreads = 256;
 
 // Raster record of one Gaussian in one view (float32). The Pluecker
@@ -131,6 +136,14 @@ struct Ws {
   int64_t chunk_stride;        // words per digit row of sort_cnt (>= chunks of capacity)
   int32_t key_bits, passes, digit_bits, key16;   // passes of digit_bits (the last maybe fewer)
   int32_t final_buf;           // which of keys/vals holds the sorted lists
+  int32_t few_chunks;          // the tile sort's scatter adds up the chunk counts itself
+};
+
+// Parts of the workspace that have to be zero (16-byte words), cleared by the
+// preprocess launch.
+struct Clear {
+  uint4 *p[2];
+  uint32_t n[2];
 };
 
 // Forward state values per pixel: K ids, K alphas, K list positions, K rgb

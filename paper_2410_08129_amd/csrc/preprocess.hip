@@ -631,13 +631,18 @@ __device__ __forceinline__ void block_total(unsigned long long v, unsigned long 
 // totals alone (44 of a Gaussian's 236 bytes read at SH degree 3, nothing
 // else written; with the fill and the scan 16 us against 38 for 200k
 // Gaussians at 800x800).
+// clr: what the later launches need zero (nothing here reads it).
 template <int DEG, bool MV, bool CULL, bool COUNT>
 __global__ void __launch_bounds__(kPreThreads) k_preprocess(GaussPtrs gp, KCfg cfg, ViewSet vs,
-                                                             Ws w) {
+                                                             Ws w, Clear clr) {
   __shared__ unsigned long long s_wsum[kPreThreads / 64];
   __shared__ CullLds s_cull[CULL ? kPreThreads / 64 : 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t blk = blockIdx.x;
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+    for (uint32_t i = blockIdx.x * kPreThreads + tid; i < clr.n[r]; i += gridDim.x * kPreThreads)
+      clr.p[r][i] = make_uint4(0u, 0u, 0u, 0u);
   const int64_t g = blk * kPreThreads + tid;
   const bool live = g < cfg.n;
   const int nviews = MV ? vs.n : 1;
@@ -730,7 +735,9 @@ __global__ void __launch_bounds__(kTotScanThreads) k_preprocess_scan(Ws w, int64
 // lane), in slot order, plus the workgroup total at the end; it first holds
 // the counts. The tile-slot descriptors get their first slots here.
 // R: entries of the digit tables.
-template <bool MV, int R>
+// ADD: pp_total holds the workgroups' totals, not their scan; each workgroup
+// adds up those before it, and the last one writes the instance count.
+template <bool MV, int R, bool ADD>
 __global__ void __launch_bounds__(kPreThreads) k_emit(KCfg cfg, ViewSet vs, Ws w) {
   constexpr int NVL = MV ? kMaxViews : 1;
   __shared__ uint32_t s_start[NVL * kPreThreads + 1];
@@ -743,10 +750,20 @@ __global__ void __launch_bounds__(kPreThreads) k_emit(KCfg cfg, ViewSet vs, Ws w
   __shared__ uint32_t s_wsum[kPreThreads / 64];
   __shared__ uint32_t s_gidx[kPreThreads];
   __shared__ uint32_t s_mark[kPreThreads / 64][64];
+  __shared__ unsigned long long s_before[kPreThreads / 64];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t blk = blockIdx.x;
-  for (int i = tid; i < w.passes * HC * (R + 1); i += kPreThreads) (&s_hist[0][0])[i] = 0u;
+  if constexpr (ADD) {
+    unsigned long long before = 0;
+    for (int64_t b = tid; b < blk; b += kPreThreads) before += w.pp_total[b];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off, 64);
+    if (lane == 0) s_before[wave] = before;
+  }
+  // (few chunks: the sort takes no histograms)
+  const int hist_passes = w.few_chunks ? 0 : w.passes;
+  for (int i = tid; i < hist_passes * HC * (R + 1); i += kPreThreads) (&s_hist[0][0])[i] = 0u;
   int64_t g;
   const bool live = gaussian_at(w, cfg, blk * kPreThreads + tid, g);
   s_gidx[tid] = (uint32_t)g;
@@ -785,7 +802,19 @@ __global__ void __launch_bounds__(kPreThreads) k_emit(KCfg cfg, ViewSet vs, Ws w
   const int nent = kPreThreads * nviews;
   if (tid == 0) s_start[nent] = block_total;
   __syncthreads();
-  const unsigned long long base = w.pp_total[blk];
+  unsigned long long base;
+  if constexpr (ADD) {
+    base = s_before[0];
+#pragma unroll
+    for (int k = 1; k < kPreThreads / 64; ++k) base += s_before[k];
+    if (tid == 0 && blk == (int64_t)gridDim.x - 1) {
+      const unsigned long long total = base + w.pp_total[blk];
+      *w.total = total;
+      if (total > (unsigned long long)w.capacity) atomicOr(&w.status[0], (uint32_t)ST_OVERFLOW);
+    }
+  } else {
+    base = w.pp_total[blk];
+  }
 
   if (live) {
     // First slot of each (view, Gaussian), clamped at 2^31 so that base +
@@ -874,7 +903,7 @@ __global__ void __launch_bounds__(kPreThreads) k_emit(KCfg cfg, ViewSet vs, Ws w
     // (one add per lane, spread over HC copies: the wave-level paths of
     // wave_hist_add cost the emit more than the conflicts they avoid)
     if (valid)
-      for (int p = 0; p < w.passes; ++p)
+      for (int p = 0; p < hist_passes; ++p)
         atomicAdd(&s_hist[p][(lane % HC) * (R + 1) +
                              ((key >> (w.digit_bits * p)) & ((1u << w.digit_bits) - 1u))], 1u);
     if (valid && e < room) {
@@ -884,7 +913,7 @@ __global__ void __launch_bounds__(kPreThreads) k_emit(KCfg cfg, ViewSet vs, Ws w
   }
   __syncthreads();
   uint32_t *hist = hist_copy(w.hist, w.passes * R);
-  for (int p = 0; p < w.passes; ++p)
+  for (int p = 0; p < hist_passes; ++p)
 #pragma unroll
     for (int d = tid; d < R; d += kPreThreads) {
       const uint32_t c = hist_total<R, HC>(s_hist[p], d);
@@ -1464,13 +1493,18 @@ hipError_t launch_fill_zero(void *p, int64_t bytes, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Up to this many preprocess workgroups (262,144 Gaussians) the emit launch adds
+// their totals up itself: at most 8 KiB read per workgroup, in place of a
+// launch of one workgroup (about 5 us).
+constexpr int kAddTotals = 1024;
+
 hipError_t launch_preprocess(const GaussPtrs &gp, const KCfg &cfg, const ViewSet &vs, const Ws &w,
-                             hipStream_t s) {
+                             const Clear &clr, hipStream_t s) {
   if (cfg.n == 0) return hipSuccess;
   const int blocks = (int)((cfg.n + kPreThreads - 1) / kPreThreads);
 #define HTGS_PRE3(D, M, C)                                                                 \
   hipLaunchKernelGGL((k_preprocess<D, M, C, false>), dim3(blocks), dim3(kPreThreads), 0, s, \
-                     gp, cfg, vs, w)
+                     gp, cfg, vs, w, clr)
 #define HTGS_PRE(D)                                                                        \
   do {                                                                                     \
     if (vs.n > 1) {                                                                        \
@@ -1493,11 +1527,16 @@ hipError_t launch_preprocess(const GaussPtrs &gp, const KCfg &cfg, const ViewSet
     hipLaunchKernelGGL(k_perm_totals, dim3(blocks), dim3(kPreThreads), 0, s, cfg, w);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_preprocess_scan, dim3(1), dim3(kTotScanThreads), 0, s, w, (int64_t)blocks);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  const bool wide = sort_radix(w.digit_bits) == 512;
-  auto *emit = vs.n > 1 ? (wide ? k_emit<true, 512> : k_emit<true, 256>)
-                        : (wide ? k_emit<false, 512> : k_emit<false, 256>);
+  const bool wide = sort_radix(w.digit_bits) == 512, add = blocks <= kAddTotals;
+  if (!add) {
+    hipLaunchKernelGGL(k_preprocess_scan, dim3(1), dim3(kTotScanThreads), 0, s, w, (int64_t)blocks);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+#define HTGS_EMIT(M)                                                                       \
+  (wide ? (add ? k_emit<M, 512, true> : k_emit<M, 512, false>)                             \
+        : (add ? k_emit<M, 256, true> : k_emit<M, 256, false>))
+  auto *emit = vs.n > 1 ? HTGS_EMIT(true) : HTGS_EMIT(false);
+#undef HTGS_EMIT
   hipLaunchKernelGGL(emit, dim3(blocks), dim3(kPreThreads), 0, s, cfg, vs, w);
   return hipGetLastError();
 }
@@ -1505,14 +1544,14 @@ hipError_t launch_preprocess(const GaussPtrs &gp, const KCfg &cfg, const ViewSet
 // The instance count alone (w.total): the preprocess without its outputs and
 // the scan of the totals.
 hipError_t launch_count(const GaussPtrs &gp, const KCfg &cfg, const ViewSet &vs, const Ws &w,
-                        hipStream_t s) {
+                        const Clear &clr, hipStream_t s) {
   if (cfg.n == 0) return hipSuccess;
   const int blocks = (int)((cfg.n + kPreThreads - 1) / kPreThreads);
   auto *count = vs.n > 1 ? (cfg.tile_cull ? k_preprocess<0, true, true, true>
                                           : k_preprocess<0, true, false, true>)
                          : (cfg.tile_cull ? k_preprocess<0, false, true, true>
                                           : k_preprocess<0, false, false, true>);
-  hipLaunchKernelGGL(count, dim3(blocks), dim3(kPreThreads), 0, s, gp, cfg, vs, w);
+  hipLaunchKernelGGL(count, dim3(blocks), dim3(kPreThreads), 0, s, gp, cfg, vs, w, clr);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_preprocess_scan, dim3(1), dim3(kTotScanThreads), 0, s, w, (int64_t)blocks);

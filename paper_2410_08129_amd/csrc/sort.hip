@@ -218,7 +218,9 @@ __global__ void __launch_bounds__(256) k_sort_scan(SortJob job, int pass) {
   }
 }
 
-template <typename KeyT, int R>
+// FEW: the digits' rows of cnt hold the chunks' counts (at most kFewChunks of
+// them), not the scanned starts.
+template <typename KeyT, int R, bool FEW>
 __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int pass, int nbits,
                                                                 const KeyT *__restrict__ kin,
                                                                 const uint32_t *__restrict__ vin,
@@ -238,12 +240,45 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int 
   const uint64_t chunk = chunk_of(blockIdx.x, nchunks);
   const uint64_t cbase = chunk * kSortChunk;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // global starts of this chunk's runs of the thread's digits (from the scan)
+  // global starts of this chunk's runs of the thread's digits
   uint32_t run_start[DP];
 #pragma unroll
-  for (int q = 0; q < DP; ++q)
-    run_start[q] = job.cnt[((size_t)pass * R + tid * DP + q) * (size_t)job.stride + chunk];
+  for (int q = 0; q < DP; ++q) {
+    const uint32_t *row = job.cnt + ((size_t)pass * R + tid * DP + q) * (size_t)job.stride;
+    if constexpr (!FEW) {
+      run_start[q] = row[chunk];   // (from the scan)
+    } else {
+      uint32_t below = 0, all = 0;
+      for (uint32_t c = 0; c < (uint32_t)nchunks; c += 4) {
+        const uint4 a = *reinterpret_cast<const uint4 *>(row + c);
+        const uint32_t u[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+          all += c + h < (uint32_t)nchunks ? u[h] : 0u;
+          below += c + h < (uint32_t)chunk ? u[h] : 0u;
+        }
+      }
+      run_start[q] = below;
+      s_off[tid * DP + q] = all;   // (each thread reads its own digits back)
+    }
+  }
   for (int i = tid; i < kSortWaves * R; i += kSortThreads) (&s_wh[0][0])[i] = 0u;
+  if constexpr (FEW) {
+    // plus the totals of the digits below
+    uint32_t mine = 0;
+#pragma unroll
+    for (int q = 0; q < DP; ++q) mine += s_off[tid * DP + q];
+    const uint32_t inc = wave_incl_add(mine);
+    if (lane == 63) s_csum[wave] = inc;
+    __syncthreads();
+    uint32_t base = inc - mine;
+    for (int k = 0; k < wave; ++k) base += s_csum[k];
+#pragma unroll
+    for (int q = 0; q < DP; ++q) {
+      run_start[q] += base;
+      base += s_off[tid * DP + q];
+    }
+  }
   __syncthreads();
 
   // Items of the chunk: nv; lane l of wave w holds item w 1024 + 64 i + l
@@ -362,8 +397,8 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int 
   }
 }
 
-// The three launches of each pass; blocks: the largest chunk count the
-// item count can reach.
+// The launches of each pass; blocks: the largest chunk count the item count
+// can reach.
 template <typename KeyT, int R>
 static hipError_t sort_passes(const SortJob &job, int key_bits, int64_t blocks, void *const *keys,
                               uint32_t *const *vals, hipStream_t s) {
@@ -377,10 +412,14 @@ static hipError_t sort_passes(const SortJob &job, int key_bits, int64_t blocks, 
                        job, p, nbits, kin);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_sort_scan<R>, dim3(R), dim3(256), 0, s, job, p);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL((k_sort_scatter<KeyT, R>), dim3((uint32_t)blocks), dim3(kSortThreads), 0, s,
-                       job, p, nbits, kin, vals[p & 1], kout, vals[(p + 1) & 1]);
+    if (blocks > kFewChunks) {
+      hipLaunchKernelGGL(k_sort_scan<R>, dim3(R), dim3(256), 0, s, job, p);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    auto *scatter = blocks > kFewChunks ? k_sort_scatter<KeyT, R, false>
+                                        : k_sort_scatter<KeyT, R, true>;
+    hipLaunchKernelGGL(scatter, dim3((uint32_t)blocks), dim3(kSortThreads), 0, s, job, p, nbits,
+                       kin, vals[p & 1], kout, vals[(p + 1) & 1]);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;
