@@ -431,14 +431,29 @@ __device__ __forceinline__ void extend_lists(uint16_t (*list)[NBATCH], int j, ui
   }
 }
 
-// Stages up to NBATCH splats of a tile's list (cnt of them from vals on) and
-// builds this wave's lists (padded with the zero row to the longest one's
-// even length). All threads of the workgroup.
+// The thread's splats of the batch from `base` on (0 past the list's end).
+// They are read a batch ahead, while the batch before is walked, so that the
+// records wait for one round trip and not for two: 6.28 -> 6.11 ms for the
+// 4K frame's launch, 393 -> 388 us at 1080p. (A load that brings the records
+// themselves nearer costs more than it hides: 411 us.)
+template <int NT, int BM>
+__device__ __forceinline__ void next_splats(const uint32_t *__restrict__ vals, uint32_t base,
+                                            uint32_t end, int tid, uint32_t *gid) {
+#pragma unroll
+  for (int i = 0; i < BM; ++i) {
+    const uint32_t j = base + (uint32_t)(i * NT + tid);
+    gid[i] = j < end ? vals[j] : 0u;
+  }
+}
+
+// Stages the batch's cnt splats (gid: this thread's, next_splats) and builds
+// this wave's lists (padded with the zero row to the longest one's even
+// length). All threads of the workgroup.
 template <int TW, int TH, int NBATCH>
 __device__ __forceinline__ BatchInfo stage_batch(FwdLds<TW, TH, NBATCH> &L,
                                                  const float *__restrict__ recs,
-                                                 const uint32_t *__restrict__ vals, int cnt,
-                                                 int px0, int py0, int wave, int lane) {
+                                                 const uint32_t *gid, int cnt, int px0, int py0,
+                                                 int wave, int lane) {
   constexpr int NT = TW * TH;
   int n[kParts];
   uint32_t reach = 0u;
@@ -456,7 +471,7 @@ __device__ __forceinline__ BatchInfo stage_batch(FwdLds<TW, TH, NBATCH> &L,
     for (int r0 = 0; r0 < NBATCH; r0 += 64) {
       const int r = r0 + lane;
       uint32_t m = 0u, e = 0u;
-      if (r < cnt) m = stage_splat(L, r, recs, vals[r], px0, py0, &e);
+      if (r < cnt) m = stage_splat(L, r, recs, gid[r0 / 64], px0, py0, &e);
       reach = max(reach, e);
       extend_lists<NBATCH>(L.list[0], r, m, n);
     }
@@ -466,7 +481,7 @@ __device__ __forceinline__ BatchInfo stage_batch(FwdLds<TW, TH, NBATCH> &L,
     const int r = wave * 64 + lane;
     if (r < cnt) {
       uint32_t e;
-      L.mask[r] = stage_splat(L, r, recs, vals[r], px0, py0, &e);
+      L.mask[r] = stage_splat(L, r, recs, gid[0], px0, py0, &e);
       L.reach[r] = e;
     }
     __syncthreads();
@@ -587,10 +602,13 @@ __device__ __forceinline__ void fwd_tile(const TileInfo &ti, const Ws &w, const 
   float *my_alpha = &s_alpha[wave][0][lane];
   if (tid < F_FLOATS / 4) L.stage[NBATCH * (F_FLOATS / 4) + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
 
+  uint32_t gid[BM];
+  next_splats<NT, BM>(vals, rg.x, rg.y, tid, gid);
   for (uint32_t base = rg.x; base < rg.y; base += NBATCH) {
     const int cnt = (int)min((uint32_t)NBATCH, rg.y - base);
     __syncthreads();
-    const BatchInfo batch = stage_batch(L, recs, vals + base, cnt, px0, py0, wave, lane);
+    const BatchInfo batch = stage_batch(L, recs, gid, cnt, px0, py0, wave, lane);
+    next_splats<NT, BM>(vals, base + NBATCH, rg.y, tid, gid);
     if (!inside) continue;
     // A splat whose mean lies at this depth or further back has no fragment
     // in front of the last core entry, and its depth is not evaluated (two
@@ -790,11 +808,14 @@ __device__ __forceinline__ void fwd_tile_sorted(const TileInfo &ti, const Ws &w,
   int nb = 0, end_pos = 0, stop_pos = -1;
   if (tid < F_FLOATS / 4) L.stage[NT * (F_FLOATS / 4) + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
 
+  uint32_t gid[1];
+  next_splats<NT, 1>(vals, rg.x, rg.y, tid, gid);
   for (uint32_t base = rg.x; base < rg.y; base += NT) {
     // (also the barrier before the stage is overwritten)
     if (__syncthreads_and(done)) break;
     const int cnt = (int)min((uint32_t)NT, rg.y - base);
-    const int nlist = stage_batch(L, recs, vals + base, cnt, px0, py0, wave, lane).nlist;
+    const int nlist = stage_batch(L, recs, gid, cnt, px0, py0, wave, lane).nlist;
+    next_splats<NT, 1>(vals, base + NT, rg.y, tid, gid);
     if (done) continue;
     const char *rows = reinterpret_cast<const char *>(L.stage);
     auto step = [&](uint32_t off, const StagedRow &row) {
