@@ -1007,7 +1007,7 @@ __device__ __forceinline__ void sh_dots(const float *__restrict__ row, const dou
 }
 
 // Writes (overwrite) or adds the gradients of Gaussian g.
-template <int NB>
+template <int NB, bool SH>
 __device__ __forceinline__ void emit_grads(const GradPtrs &gr, int64_t g, const float gmu[3],
                                            const float gls[3], const float gq[4], float glogit,
                                            const float *gsh, bool overwrite) {
@@ -1019,7 +1019,7 @@ __device__ __forceinline__ void emit_grads(const GradPtrs &gr, int64_t g, const 
     if (gr.quats)
       reinterpret_cast<float4 *>(gr.quats)[g] = make_float4(gq[0], gq[1], gq[2], gq[3]);
     if (gr.logits) gr.logits[g] = glogit;
-    if (gr.sh) {
+    if (SH && gr.sh) {
       float *dst = gr.sh + g * NB * 3;
       if constexpr ((3 * NB) % 4 == 0) {
         float4 *d4 = reinterpret_cast<float4 *>(dst);
@@ -1042,7 +1042,49 @@ __device__ __forceinline__ void emit_grads(const GradPtrs &gr, int64_t g, const 
       reinterpret_cast<float4 *>(gr.quats)[g] = t;
     }
     if (gr.logits) gr.logits[g] += glogit;
-    if (gr.sh) add_row<3 * NB>(gr.sh + g * NB * 3, gsh);
+    if (SH && gr.sh) add_row<3 * NB>(gr.sh + g * NB * 3, gsh);
+  }
+}
+
+// A wave's SH gradient rows of degree 3 (48 floats each, 12 KiB in one piece)
+// go through LDS in halves of 24 floats, so that a load or store of the wave
+// covers 1 KiB in runs of 96 bytes; with a row per lane each one touches
+// 64 lines for 16 bytes. Sorted blending's chain rule, 1M Gaussians at
+// 1280x720: 227 -> 210 us with the sums. The form that also scans the
+// partials stays with a row per lane: the registers this takes cost it its
+// third wave per SIMD (210 -> 219 us at 1080p), or spills where it is held
+// to three (211 us; 4K frame 1.94 -> 2.01 ms).
+constexpr int kHalfRow = 24, kHalfStride = 28;   // floats; rows 16-byte aligned, no bank conflicts
+
+// The gradient rows (gsh: this lane's) of the Gaussians in `rows` (bit l: lane
+// l's) added to dst, or written. buf: 64 * kHalfStride floats of the wave's
+// own. All 64 lanes.
+__device__ __forceinline__ void emit_sh_rows(float *__restrict__ dst, const float *gsh,
+                                             unsigned long long rows, bool overwrite, float *buf,
+                                             int lane) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    float4 *d4 = reinterpret_cast<float4 *>(dst + kHalfRow * h);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+      *reinterpret_cast<float4 *>(buf + lane * kHalfStride + 4 * k) =
+          make_float4(gsh[kHalfRow * h + 4 * k], gsh[kHalfRow * h + 4 * k + 1],
+                      gsh[kHalfRow * h + 4 * k + 2], gsh[kHalfRow * h + 4 * k + 3]);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+      const int p = i * 64 + lane, row = p / 6, col = p - 6 * row;
+      if (((rows >> row) & 1ull) == 0ull) continue;
+      float4 *d = d4 + row * 12 + col;
+      float4 v = *reinterpret_cast<const float4 *>(buf + row * kHalfStride + 4 * col);
+      if (!overwrite) {
+        const float4 t = *d;
+        v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
+      }
+      *d = v;
+    }
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
@@ -1236,9 +1278,11 @@ template <int DEG, bool MV, bool SUMMED>
 __global__ void __launch_bounds__(256, MV ? 2 : 1) k_preprocess_bwd(GaussPtrs gp, GradPtrs gr, KCfg cfg,
                                                          ViewSet vs, Ws w) {
   constexpr int NB = (DEG + 1) * (DEG + 1);
+  constexpr bool ROWS = DEG == 3 && SUMMED;   // (see emit_sh_rows)
   __shared__ float s_acc[SUMMED ? 1 : 4][kPartialFloats][64];
   __shared__ uint32_t s_mark[SUMMED ? 1 : 4][64];
-  const int wave = SUMMED ? 0 : threadIdx.x >> 6, lane = threadIdx.x & 63;
+  __shared__ __attribute__((aligned(16))) float s_rows[ROWS ? 4 : 1][64 * kHalfStride];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t pos0 = g - lane;
   if (pos0 >= cfg.n) return;  // uniform over the wave
@@ -1395,6 +1439,9 @@ __global__ void __launch_bounds__(256, MV ? 2 : 1) k_preprocess_bwd(GaussPtrs gp
       __builtin_amdgcn_wave_barrier();
     }
   }
+  if (ROWS && gr.sh)
+    emit_sh_rows(gr.sh + pos0 * 3 * NB, gsh, __ballot(cfg.grad_overwrite ? live : total != 0),
+                 cfg.grad_overwrite != 0, s_rows[ROWS ? wave : 0], lane);
   if (!live) return;
   if (ok) {
     // running sums for densification: always added to (they gather over
@@ -1413,7 +1460,7 @@ __global__ void __launch_bounds__(256, MV ? 2 : 1) k_preprocess_bwd(GaussPtrs gp
       float zsh[3 * NB];
 #pragma unroll
       for (int k = 0; k < 3 * NB; ++k) zsh[k] = 0.f;
-      emit_grads<NB>(gr, g, z, z, z, 0.f, zsh, true);
+      emit_grads<NB, !ROWS>(gr, g, z, z, z, 0.f, zsh, true);
     }
     return;
   }
@@ -1456,7 +1503,7 @@ __global__ void __launch_bounds__(256, MV ? 2 : 1) k_preprocess_bwd(GaussPtrs gp
     fls[k] = (float)gl[k];
   }
   for (int k = 0; k < 4; ++k) fq[k] = (float)((gqn[k] - qn[k] * proj) * iq);
-  emit_grads<NB>(gr, g, fmu, fls, fq, (float)glogit, gsh, cfg.grad_overwrite != 0);
+  emit_grads<NB, !ROWS>(gr, g, fmu, fls, fq, (float)glogit, gsh, cfg.grad_overwrite != 0);
 }
 
 // Opacity decay (Sec. 4.2): o <- lambda o on the logits, x' =
