@@ -1019,9 +1019,12 @@ __device__ __forceinline__ void write_partials(const float *acc, float a, float 
 // for fewer waves. One-block tiles with 1, 2, 3 and 4 waves: 516, 516, 532
 // and 556 us at 1080p (205 instances per tile), 8.78, 7.80, 7.90 and 8.00 ms
 // on the 4K frame (786 per tile).
-template <int TW, int TH>
+// WIDE: for frames of few tiles, whose workgroups do not fill the chip, so
+// that the chunks of a long list are walked side by side (the sums do not
+// depend on which wave walks a chunk).
+template <int TW, int TH, bool WIDE>
 constexpr int bwd_waves() {
-  return TW * TH <= 64 ? 2 : 4;
+  return WIDE ? 8 : (TW * TH <= 64 ? 2 : 4);
 }
 
 // Target waves per SIMD of the backward (register budget; HIP's second
@@ -1042,7 +1045,7 @@ constexpr int bwd_simd_waves() {
 // formed the code table's addresses lane by lane, tested the clamp and the
 // smallest |d|^2 for every pixel and wrote 64 scattered partials per store;
 // K = 16 with 16x8 tiles 941 -> 722 us, the 4K frame (K = 16) 8.88 -> 7.61 ms.
-template <int KMAX, int TW, int TH, bool EXACT>
+template <int KMAX, int TW, int TH, bool WIDE, bool EXACT>
 __device__ __forceinline__ void bwd_tile(const TileInfo &ti, const Ws &w, const ViewSet &vs,
                                          const KCfg &cfg, const float *__restrict__ state,
                                          const uint32_t *__restrict__ vals, uint32_t &nfr) {
@@ -1051,7 +1054,7 @@ __device__ __forceinline__ void bwd_tile(const TileInfo &ti, const Ws &w, const 
   constexpr int BX = TW / 8;
   using L = PixLayout<KMAX>;
   __shared__ float4 s_pix[NT * L::kStride / 4];
-  constexpr int BW = bwd_waves<TW, TH>();
+  constexpr int BW = bwd_waves<TW, TH, WIDE>();
   constexpr int BT = 64 * BW;
   // Per wave, for the 8x8 block being walked, the fragment codes of its
   // pixels by the chunk's instances: codes[wave][r][2 lane], [2 lane + 1]
@@ -1160,21 +1163,22 @@ __device__ __forceinline__ void bwd_tile(const TileInfo &ti, const Ws &w, const 
   const uint32_t nch = (count + 63u) >> 6;
   const float amax = cfg.alpha_max;
   // Chunk schedule. In general a wave takes every BW-th chunk over all of
-  // the tile's 8x8 blocks. With two blocks and four waves (16x8, 8x16
-  // tiles) a pair of waves shares each chunk instead, one block each, and
-  // the pairs alternate chunks; the block-1 wave hands its sums to the
+  // the tile's 8x8 blocks. With two blocks (16x8 tiles) a pair of waves
+  // shares each chunk instead, one block each, and the pairs take the
+  // chunks in turn; the block-1 wave hands its sums to the
   // block-0 wave, which writes the partial. A tile whose chunk count is not
   // a multiple of the wave count then leaves fewer waves idle.
-  constexpr bool PAIRS = (NB == 2 && BW == 4);
-  const int myblk = PAIRS ? (wave >> 1) : -1;
-  const uint32_t c_end = PAIRS ? 2u * ((nch + 1u) >> 1) : nch;  // uniform per block when PAIRS
-  const uint32_t c_step = PAIRS ? 2u : (uint32_t)BW;
+  constexpr bool PAIRS = NB == 2;
+  constexpr uint32_t NP = BW / 2;   // pairs
+  const int myblk = PAIRS ? wave / (int)NP : -1;
+  const uint32_t c_end = PAIRS ? NP * ((nch + NP - 1u) / NP) : nch;  // uniform when PAIRS
+  const uint32_t c_step = PAIRS ? NP : (uint32_t)BW;
   const int cx2 = 2 * px0 + TW - 1, cy2 = 2 * py0 + TH - 1;
   const float hx = 0.5f * (float)(TW - 1), hy = 0.5f * (float)(TH - 1);
   // The factors are complete at the first chunk's barrier, behind its loads
   // and staging: the waves without pixels of their own do those meanwhile.
   bool ready = false;
-  for (uint32_t c = PAIRS ? (uint32_t)(wave & 1) : (uint32_t)wave; c < c_end; c += c_step) {
+  for (uint32_t c = PAIRS ? (uint32_t)wave % NP : (uint32_t)wave; c < c_end; c += c_step) {
     const uint32_t j = rg.x + c * 64u + lane;
     const bool active = c < nch && j < rg.y;
     // The forward's staged forms of |d|^2 and |m|^2 for this (tile, splat)
@@ -1337,7 +1341,7 @@ __device__ __forceinline__ void bwd_tile(const TileInfo &ti, const Ws &w, const 
     nfr += (uint32_t)nf;
     if constexpr (PAIRS) {
       // The block-1 wave's code table is free now: it carries the sums.
-      float *xch = reinterpret_cast<float *>(&s_code[2 + (wave & 1)][0][0]);
+      float *xch = reinterpret_cast<float *>(&s_code[PAIRS ? (int)NP + wave % (int)NP : 0][0][0]);
       if (myblk == 1) {
 #pragma unroll
         for (int k = 0; k < 16; ++k) xch[k * 64 + lane] = acc[k];
@@ -1379,15 +1383,15 @@ __global__ void __launch_bounds__((TW * TH), (fwd_simd_waves<KMAX, TW, TH, BM>()
   if (tile_info(vs, cfg, w, ti)) fwd_tile<KMAX, TW, TH, BM, EXACT>(ti, w, vs, cfg, state, vals);
 }
 
-template <int KMAX, int TW, int TH, bool EXACT>
-__global__ void __launch_bounds__((64 * bwd_waves<TW, TH>()), (bwd_simd_waves<KMAX, TW, TH>()))
+template <int KMAX, int TW, int TH, bool WIDE, bool EXACT>
+__global__ void __launch_bounds__((64 * bwd_waves<TW, TH, WIDE>()), (bwd_simd_waves<KMAX, TW, TH>()))
     k_raster_bwd(Ws w, ViewSet vs, KCfg cfg, const float *__restrict__ state,
                  const uint32_t *__restrict__ vals) {
   // the forward of a failed front end rendered empty tiles: nothing to do
   if (front_failed(w)) return;
   uint32_t nfr = 0;   // fragments this thread differentiated
   TileInfo ti;
-  if (tile_info(vs, cfg, w, ti)) bwd_tile<KMAX, TW, TH, EXACT>(ti, w, vs, cfg, state, vals, nfr);
+  if (tile_info(vs, cfg, w, ti)) bwd_tile<KMAX, TW, TH, WIDE, EXACT>(ti, w, vs, cfg, state, vals, nfr);
   // one atomic per wave (a word of LDS would take the 8x8 and 16x8 kernels
   // past 16 and 32 KiB, one workgroup per CU fewer)
 #pragma unroll
@@ -1684,11 +1688,22 @@ static hipError_t fwd_launch(const Ws &w, const ViewSet &vs, const KCfg &cfg, fl
   return fwd_launch_bm<KMAX, TW, TH, 1, EXACT>(w, vs, cfg, state, vals, s);
 }
 
+// Frames of up to this many tiles take the wide backward. It wins while the
+// tiles leave CUs without work and loses where they do not, as its workgroups
+// need more LDS: 8x8 tiles, 1024 of them 31.5 -> 28.0 us and 2048 32.1 -> 42.1;
+// 16x8 512 49.1 -> 35.4, 1024 44.8 -> 52.4; 16x16 64 133 -> 78, 1024 256 ->
+// 177, 2000 184 -> 202 (50k to 300k Gaussians).
+template <int TW, int TH>
+constexpr int few_tiles() {
+  return TW * TH == 128 ? 512 : 1024;
+}
 template <int KMAX, int TW, int TH, bool EXACT>
 static hipError_t bwd_launch(const Ws &w, const ViewSet &vs, const KCfg &cfg, const float *state,
                              const uint32_t *vals, hipStream_t s) {
-  constexpr int BT = 64 * bwd_waves<TW, TH>();
-  hipLaunchKernelGGL((k_raster_bwd<KMAX, TW, TH, EXACT>), tile_grid(vs, cfg), dim3(BT), 0, s, w, vs, cfg, state, vals);
+  const bool wide = vs.total_tiles <= few_tiles<TW, TH>();
+  auto *bwd = wide ? k_raster_bwd<KMAX, TW, TH, true, EXACT> : k_raster_bwd<KMAX, TW, TH, false, EXACT>;
+  const int threads = 64 * (wide ? bwd_waves<TW, TH, true>() : bwd_waves<TW, TH, false>());
+  hipLaunchKernelGGL(bwd, tile_grid(vs, cfg), dim3(threads), 0, s, w, vs, cfg, state, vals);
   return hipGetLastError();
 }
 
