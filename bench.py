@@ -212,7 +212,10 @@ def run_single(args):
     kmax = next(k for k in (1, 2, 4, 8, 16, 32) if k >= max(st.K, 1))
     exact = "true" if st.K == kmax else "false"
     if dom == "raster_bwd":
-        key = f"k_raster_bwd<{kmax}, {st.tile_w}, {st.tile_h}, {exact}>"
+        # (the form for frames of few tiles has "true" before the last argument)
+        few = tiles_x * tiles_y <= (512 if st.tile_w * st.tile_h == 128 else 1024)
+        key = (f"k_raster_bwd<{kmax}, {st.tile_w}, {st.tile_h}, {'true' if few else 'false'}, "
+               f"{exact}>")
     else:
         bm = 2 if st.lds_batch == 2 * st.tile_w * st.tile_h else 1
         key = f"k_raster_fwd<{kmax}, {st.tile_w}, {st.tile_h}, {bm}, {exact}>"

@@ -8,8 +8,8 @@
 //    Sec. 3.2 (s, f, p_i, h_i), all in float64 so that the tile lists are
 //    exact; pixel-centre rect -> tile rect -> instance count;
 //  * the affine Pluecker record for the rasterizer and the SH colour.
-// A one-workgroup launch then scans the workgroups' instance totals, and an
-// emit launch writes the (tile key, Gaussian index) instances with a
+// A one-workgroup launch then scans the workgroups' instance totals (the emit
+// launch adds them up itself where they are few), and the emit launch writes the (tile key, Gaussian index) instances with a
 // load-balanced loop and adds the radix-sort digit histograms of those
 // keys. No workgroup waits for another.
 //

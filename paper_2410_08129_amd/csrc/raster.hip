@@ -561,7 +561,12 @@ __device__ __forceinline__ void add_fragments(const Ws &w, uint32_t n, int lane)
   if (lane == 0 && n) count_add(w.frags, (unsigned long long)n);
 }
 
-// One tile. EXACT: K == KMAX, known at compile time.
+// One tile. EXACT: K == KMAX, known at compile time. Bound by VALU issue (93%
+// of the cycles on the 4K frame with K = 16: about 36 instructions per step of
+// the walk, 36 more where a lane inserts, 375 per staged batch) with 4.5 waves
+// per SIMD, which LDS sets. 1080p, K = 8, 8x8 tiles: 525 us when each block
+// walked one list and shifted its core by compares and selects, 384 now; 4K
+// frame 8.30 -> 6.10 ms, 8 views 1180 -> 687 us.
 template <int KMAX, int TW, int TH, int BM, bool EXACT>
 __device__ __forceinline__ void fwd_tile(const TileInfo &ti, const Ws &w, const ViewSet &vs,
                                          const KCfg &cfg, float *__restrict__ state,
@@ -1030,7 +1035,7 @@ constexpr int bwd_waves() {
 // Target waves per SIMD of the backward (register budget; HIP's second
 // launch-bounds argument is a minimum number of waves per execution unit).
 // The walk of a one-block tile with K <= 8 fits 96 registers; at 80 it
-// spills (630 against 516 us at 1080p). Larger cores and tiles fit 128,
+// spills (630 against 516 us at 1080p; now 488). Larger cores and tiles fit 128,
 // except where LDS allows no more than two or three waves anyway.
 template <int KMAX, int TW, int TH>
 constexpr int bwd_simd_waves() {
@@ -1038,13 +1043,15 @@ constexpr int bwd_simd_waves() {
 }
 
 // One tile of the backward. At 1080p (1M Gaussians, K = 8, 8x8 tiles) the
-// walk's VALU work (about 420 us) and the memory traffic (490 us with the
-// walk left out: 0.45 GB of state, 0.85 GB of records, a descriptor per
-// instance, and 230 us for 0.42 GB of partials in random 64-byte slots)
-// overlap to 516 us. The launch took 602 us with a branch per fragment that
+// walk's VALU work overlaps with the memory traffic (358 us with the walk left
+// out: 143 of them for 0.42 GB of partials in random 64-byte slots, 40 for a
+// 16-byte descriptor in a random line per instance, the rest 0.45 GB of state
+// and 0.85 GB of records) to 488 us; on the 4K frame (K = 16) 5.6 of 7.4 ms
+// remain without it. The launch took 602 us with a branch per fragment that
 // formed the code table's addresses lane by lane, tested the clamp and the
-// smallest |d|^2 for every pixel and wrote 64 scattered partials per store;
-// K = 16 with 16x8 tiles 941 -> 722 us, the 4K frame (K = 16) 8.88 -> 7.61 ms.
+// smallest |d|^2 for every pixel and wrote 64 scattered partials per store,
+// and 514 before the state and the partials became non-temporal; K = 16
+// with 16x8 tiles 941 -> 690 us, the 4K frame 8.83 -> 7.40 ms.
 template <int KMAX, int TW, int TH, bool WIDE, bool EXACT>
 __device__ __forceinline__ void bwd_tile(const TileInfo &ti, const Ws &w, const ViewSet &vs,
                                          const KCfg &cfg, const float *__restrict__ state,

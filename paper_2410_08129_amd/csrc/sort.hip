@@ -4,8 +4,9 @@
 // blending (the 3DGS order that the paper's "w/o per-pixel HT"
 // configuration blends in, Sec. 4.3, Table splat_eval).
 //
-// Three launches per digit of at most 9 bits, none of whose workgroups waits
-// for another. The keys are cut into chunks of 4096 in list order.
+// Three launches per digit of at most 9 bits (two where the chunks are few:
+// the scatter then adds up their counts itself), none of whose workgroups
+// waits for another. The keys are cut into chunks of 4096 in list order.
 //   count:   each workgroup counts the digits of its chunk (LDS adds) and
 //            stores the counts into a digit-major table;
 //   scan:    one workgroup per digit turns its row of chunk counts into the
