@@ -70,13 +70,13 @@ Layout make_layout(int64_t n, int n_views, int64_t total_tiles, int64_t capacity
   L.total = o; o = align_up(o + 8);   // instance count
   L.frags = o; o = align_up(o + 2 * 8 * kCounterSpread * kCounterStride);  // fragment counters
   L.pp_total = o; o = align_up(o + 8 * ((n + kPreThreads - 1) / kPreThreads));
-  L.hist = o; o = align_up(o + kHistCopies * L.passes * radix * 4);
+  L.hist = o; o = align_up(o + hist_copies((int)radix) * L.passes * radix * 4);
   L.ranges = o; o = align_up(o + 8 * total_tiles);
   L.order_hist = o; o = align_up(o + 2 * 32 * 4);
-  L.dhist = o; o = align_up(o + (sorted ? kHistCopies * 4 * 256 * 4 : 0));
+  L.dhist = o; o = align_up(o + (sorted ? hist_copies(256) * 4 * 256 * 4 : 0));
   L.zero_end = o;
-  L.sort_cnt = o; o = align_up(o + (int64_t)L.passes * radix * L.chunk_stride * 4);
-  L.dcnt = o; o = align_up(o + 4 * 256 * L.dchunk_stride * 4);
+  L.sort_cnt = o; o = align_up(o + radix * L.chunk_stride * 4);
+  L.dcnt = o; o = align_up(o + 256 * L.dchunk_stride * 4);
   L.records = o; o = align_up(o + (int64_t)n_views * n * kRecFloats * 4);
   L.rects = o; o = align_up(o + (int64_t)n_views * n * 16);
   L.refpix = o; o = align_up(o + (int64_t)n_views * n * 4);

@@ -107,8 +107,8 @@ struct Ws {
   unsigned long long *frags;   // fragments counted by the forward raster (spread, below)
   unsigned long long *frags_bwd;  // fragments counted by the backward raster (spread)
   unsigned long long *pp_total;  // per preprocess workgroup: its instance total, then its first slot
-  uint32_t *hist;              // [kHistCopies][passes][radix] digit histograms (summed when read)
-  uint32_t *sort_cnt;          // [passes][radix][chunk_stride]: per-chunk digit counts, then
+  uint32_t *hist;              // [hist_copies][passes][radix] digit histograms (summed when read)
+  uint32_t *sort_cnt;          // [radix][chunk_stride]: a pass' per-chunk digit counts, then
                                // the global start of each (digit, chunk) run
   uint2 *ranges;               // [total_tiles] (start, end)
   uint32_t *order_hist;        // [2][32] cost-bucket counts and cursors
@@ -127,8 +127,8 @@ struct Ws {
   // emit launch walks), its digit histograms and per-chunk counts.
   uint32_t *dkeys[2];
   uint32_t *dvals[2];
-  uint32_t *dhist;             // [kHistCopies][4][256] (four passes of 8 bits)
-  uint32_t *dcnt;              // [4][256][dchunk_stride]
+  uint32_t *dhist;             // [hist_copies][4][256] (four passes of 8 bits)
+  uint32_t *dcnt;              // [256][dchunk_stride]
   const uint32_t *perm;        // Gaussians front to back (null: index order)
   uint32_t *counts;            // instances per Gaussian (in dkeys[0], after the depth sort)
   int64_t dchunk_stride;
@@ -155,15 +155,17 @@ __host__ __device__ constexpr int state_values(int K) { return 6 * K + 6; }
 // left out (-1: none).
 constexpr int kSortedStateValues = 7;
 
-// Digit histograms: kHistCopies copies, added to by workgroup
-// blockIdx % kHistCopies and summed by the sort's scan. With one copy the
+// Digit histograms: 64 copies (48 of 9-bit digits, so that two passes of them
+// take no more room than three of 8 bits), added to by workgroup
+// blockIdx % copies and summed by the sort's scan. With one copy the
 // emit launch's end-of-workgroup adds (one per non-empty digit, ~24 per
 // workgroup) queued on 16 cache lines and set its length (87 us at 1080p).
-constexpr int kHistCopies = 64;
+__host__ __device__ constexpr int hist_copies(int radix) { return radix == 512 ? 48 : 64; }
 // Copy of a histogram of `words` digits (over all passes) that this
 // workgroup adds to.
+template <int R>
 __device__ __forceinline__ uint32_t *hist_copy(uint32_t *hist, int words) {
-  return hist + (blockIdx.x % kHistCopies) * words;
+  return hist + (blockIdx.x % hist_copies(R)) * words;
 }
 
 // Radix sort digits: 8 bits at most, the passes as even as possible; 9 bits

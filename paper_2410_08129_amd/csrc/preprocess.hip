@@ -912,7 +912,7 @@ __global__ void __launch_bounds__(kPreThreads) k_emit(KCfg cfg, ViewSet vs, Ws w
     }
   }
   __syncthreads();
-  uint32_t *hist = hist_copy(w.hist, w.passes * R);
+  uint32_t *hist = hist_copy<R>(w.hist, w.passes * R);
   for (int p = 0; p < hist_passes; ++p)
 #pragma unroll
     for (int d = tid; d < R; d += kPreThreads) {

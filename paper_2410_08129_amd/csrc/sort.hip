@@ -36,8 +36,8 @@ struct SortJob {
   const unsigned long long *count;  // null: n_fixed items
   uint64_t n_fixed;
   int64_t capacity;
-  const uint32_t *hist;             // [kHistCopies][passes][radix]
-  uint32_t *cnt;                    // [passes][radix][stride]: digit counts per chunk, then
+  const uint32_t *hist;             // [hist_copies][passes][radix]
+  uint32_t *cnt;                    // [radix][stride]: the pass' digit counts per chunk, then
                                     // the global start of each (digit, chunk) run
   int64_t stride;
   int32_t passes, digit_bits;
@@ -153,7 +153,7 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_count(SortJob job, int pa
   __syncthreads();
 #pragma unroll
   for (int d = tid; d < R; d += kSortThreads)
-    job.cnt[((size_t)pass * R + d) * (size_t)job.stride + chunk] = hist_total<R>(s_cnt, d);
+    job.cnt[(size_t)d * (size_t)job.stride + chunk] = hist_total<R>(s_cnt, d);
 }
 
 // One workgroup per digit: exclusive scan of its row of chunk counts, plus
@@ -175,7 +175,7 @@ __global__ void __launch_bounds__(256) k_sort_scan(SortJob job, int pass) {
     if (d0 + tid < (int)dg) {
       const uint32_t *h = job.hist + pass * R + d0 + tid;
 #pragma unroll
-      for (int c = 0; c < kHistCopies; ++c) x += h[c * copy];
+      for (int c = 0; c < hist_copies(R); ++c) x += h[c * copy];
     }
   const uint32_t wx = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_add(x), 63);
   if (lane == 0) s_wsum[wave] = wx;
@@ -183,7 +183,7 @@ __global__ void __launch_bounds__(256) k_sort_scan(SortJob job, int pass) {
   if (tid == 0) s_base = s_wsum[0] + s_wsum[1] + s_wsum[2] + s_wsum[3];
   __syncthreads();
   uint32_t carry = s_base;
-  uint32_t *row = job.cnt + ((size_t)pass * R + dg) * (size_t)job.stride;
+  uint32_t *row = job.cnt + (size_t)dg * (size_t)job.stride;
   for (uint64_t c0 = 0; c0 < nchunks; c0 += 256 * kScanItems) {
     const uint64_t cb = c0 + (uint64_t)tid * kScanItems;
     uint32_t v[kScanItems];
@@ -245,7 +245,7 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int 
   uint32_t run_start[DP];
 #pragma unroll
   for (int q = 0; q < DP; ++q) {
-    const uint32_t *row = job.cnt + ((size_t)pass * R + tid * DP + q) * (size_t)job.stride;
+    const uint32_t *row = job.cnt + (size_t)(tid * DP + q) * (size_t)job.stride;
     if constexpr (!FEW) {
       run_start[q] = row[chunk];   // (from the scan)
     } else {
@@ -580,7 +580,7 @@ __global__ void __launch_bounds__(256) k_depth_keys(const float *__restrict__ me
     for (int p = 0; p < 4; ++p) wave_hist_add<R>(s_hist[p], (key >> (8 * p)) & 255u, valid, 8);
   }
   __syncthreads();
-  uint32_t *hc = hist_copy(hist, 4 * R);
+  uint32_t *hc = hist_copy<R>(hist, 4 * R);
   for (int i = threadIdx.x; i < 4 * R; i += blockDim.x) {
     const uint32_t c = hist_total<R>(s_hist[i >> 8], i & 255);
     if (c) atomicAdd(&hc[i], c);
