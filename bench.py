@@ -212,8 +212,8 @@ def run_single(args):
     kmax = next(k for k in (1, 2, 4, 8, 16, 32) if k >= max(st.K, 1))
     exact = "true" if st.K == kmax else "false"
     if dom == "raster_bwd":
-        # (the form for frames of few tiles has "true" before the last argument)
-        few = tiles_x * tiles_y <= (512 if st.tile_w * st.tile_h == 128 else 1024)
+        # (the form for few tiles of long lists has "true" before the last argument)
+        few = tiles_x * tiles_y <= 512 and keys.size > 64 * tiles_x * tiles_y
         key = (f"k_raster_bwd<{kmax}, {st.tile_w}, {st.tile_h}, {'true' if few else 'false'}, "
                f"{exact}>")
     else:

@@ -1695,19 +1695,21 @@ static hipError_t fwd_launch(const Ws &w, const ViewSet &vs, const KCfg &cfg, fl
   return fwd_launch_bm<KMAX, TW, TH, 1, EXACT>(w, vs, cfg, state, vals, s);
 }
 
-// Frames of up to this many tiles take the wide backward. It wins while the
-// tiles leave CUs without work and loses where they do not, as its workgroups
-// need more LDS: 8x8 tiles, 1024 of them 31.5 -> 28.0 us and 2048 32.1 -> 42.1;
-// 16x8 512 49.1 -> 35.4, 1024 44.8 -> 52.4; 16x16 64 133 -> 78, 1024 256 ->
-// 177, 2000 184 -> 202 (50k to 300k Gaussians).
-template <int TW, int TH>
-constexpr int few_tiles() {
-  return TW * TH == 128 ? 512 : 1024;
+// Frames of up to this many tiles take the wide backward: two workgroups per
+// CU, which registers and LDS allow for every core size, so that all tiles run
+// at once. Past it the wide form loses where lists are short (1200 tiles of
+// 16x16, K = 8: 84 -> 119 us with 50k Gaussians, 216 -> 178 with 300k; 2048 of
+// 8x8 32 -> 42), below it wins where they are long (50k Gaussians, 192
+// tiles of 8x8 46 -> 22 us, 128 of 16x16 87 -> 62, 512 of 16x8 49 -> 35). With
+// room for less than a chunk per tile there is nothing to share.
+constexpr int kFewTiles = 512;
+static bool few_tiles(const Ws &w, const ViewSet &vs) {
+  return vs.total_tiles <= kFewTiles && w.capacity > (int64_t)64 * vs.total_tiles;
 }
 template <int KMAX, int TW, int TH, bool EXACT>
 static hipError_t bwd_launch(const Ws &w, const ViewSet &vs, const KCfg &cfg, const float *state,
                              const uint32_t *vals, hipStream_t s) {
-  const bool wide = vs.total_tiles <= few_tiles<TW, TH>();
+  const bool wide = few_tiles(w, vs);
   auto *bwd = wide ? k_raster_bwd<KMAX, TW, TH, true, EXACT> : k_raster_bwd<KMAX, TW, TH, false, EXACT>;
   const int threads = 64 * (wide ? bwd_waves<TW, TH, true>() : bwd_waves<TW, TH, false>());
   hipLaunchKernelGGL(bwd, tile_grid(vs, cfg), dim3(threads), 0, s, w, vs, cfg, state, vals);
