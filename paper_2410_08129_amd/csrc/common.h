@@ -9,9 +9,18 @@ namespace htgs {
 constexpr int kMaxViews = 16;
 constexpr int kRecFloats = 32;      // per (view, Gaussian) raster record
 constexpr int kPartialFloats = 16;  // per-instance backward partials (64 bytes)
-constexpr int kSortThreads = 256;
-constexpr int kSortItems = 16;
-constexpr int kSortChunk = kSortThreads * kSortItems;
+// Keys per workgroup of a sort pass, and its threads: a chunk's ranking is a
+// chain over a thread's keys, so more threads end it sooner, and fewer cost
+// less LDS. 256, 512 and 1024 threads: both passes of the 1080p tile sort
+// (1,608 chunks) 82, 72 and 85 us, the 4K frame's (24,900) 1.24, 1.20 and
+// 1.22 ms, the 720p frame's (896) 58, 53 and 58 us. Where all chunks that there
+// is room for are resident at once (two workgroups per CU) 1024 win: four
+// passes over 1M depth keys (245) 101, 86 and 83 us, a 637x479 frame's tile
+// sort 40, 28 and 26.
+constexpr int kSortChunk = 4096;
+constexpr int kSortThreads = 512;
+constexpr int kSortThreadsFew = 1024;
+constexpr int kResidentChunks = 512;
 // Up to this many chunks of room, the scatter reads the digits' rows of chunk
 // counts whole (256 bytes each) and adds them up, and a pass takes two launches
 // instead of three (about 5 us each). Past one line per digit the rows'

@@ -26,7 +26,6 @@
 
 namespace htgs {
 
-constexpr int kSortWaves = kSortThreads / 64;
 constexpr int kScanItems = 8;   // chunk counts per thread per round of the scan
 
 // What a sort works on: the item count (a device word, or a fixed number),
@@ -106,9 +105,10 @@ __device__ __forceinline__ T load_at(const T *base, uint32_t i) {
                                       (uint32_t)(i * (uint32_t)sizeof(T)));
 }
 
-template <typename KeyT, int R>
-__global__ void __launch_bounds__(kSortThreads) k_sort_count(SortJob job, int pass, int nbits,
+template <typename KeyT, int R, int NT>
+__global__ void __launch_bounds__(NT) k_sort_count(SortJob job, int pass, int nbits,
                                                               const KeyT *__restrict__ kin) {
+  constexpr int ITEMS = kSortChunk / NT;
   __shared__ uint32_t s_cnt[kHistLaneCopies * (R + 1)];
   uint64_t I;
   if (!sort_items(job, I)) return;
@@ -117,42 +117,55 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_count(SortJob job, int pa
   const uint64_t chunk = chunk_of(blockIdx.x, nchunks);
   const uint64_t cbase = chunk * kSortChunk;
   const int tid = threadIdx.x;
-  for (int i = tid; i < kHistLaneCopies * (R + 1); i += kSortThreads) s_cnt[i] = 0u;
+  for (int i = tid; i < kHistLaneCopies * (R + 1); i += NT) s_cnt[i] = 0u;
   const int shift = job.digit_bits * pass;
-  uint32_t dg[kSortItems];
+  uint32_t dg[ITEMS];
   const bool whole = cbase + kSortChunk <= I;
   if (whole) {
-    // the order of the keys does not matter here: 16-byte loads
-    constexpr int kPer = 16 / (int)sizeof(KeyT);
-    const uint4 *src = reinterpret_cast<const uint4 *>(kin + cbase);
+    // the order of the keys does not matter here: 16-byte loads (8-byte ones
+    // where a thread has only four 16-bit keys)
+    if constexpr (ITEMS * sizeof(KeyT) >= 16) {
+      constexpr int kPer = 16 / (int)sizeof(KeyT);
+      static_assert(ITEMS % kPer == 0, "whole loads");
+      const uint4 *src = reinterpret_cast<const uint4 *>(kin + cbase);
 #pragma unroll
-    for (int j = 0; j < kSortItems / kPer; ++j) {
-      const uint4 q = src[j * kSortThreads + tid];
-      const uint32_t u[4] = {q.x, q.y, q.z, q.w};
+      for (int j = 0; j < ITEMS / kPer; ++j) {
+        const uint4 q = src[j * NT + tid];
+        const uint32_t u[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        if constexpr (sizeof(KeyT) == 2) {
-          dg[j * kPer + 2 * h] = digit_of(u[h] & 0xffffu, shift, nbits);
-          dg[j * kPer + 2 * h + 1] = digit_of(u[h] >> 16, shift, nbits);
-        } else {
-          dg[j * kPer + h] = digit_of(u[h], shift, nbits);
+        for (int h = 0; h < 4; ++h) {
+          if constexpr (sizeof(KeyT) == 2) {
+            dg[j * kPer + 2 * h] = digit_of(u[h] & 0xffffu, shift, nbits);
+            dg[j * kPer + 2 * h + 1] = digit_of(u[h] >> 16, shift, nbits);
+          } else {
+            dg[j * kPer + h] = digit_of(u[h], shift, nbits);
+          }
         }
+      }
+    } else {
+      static_assert(ITEMS == 4 && sizeof(KeyT) == 2, "one 8-byte load");
+      const uint2 q = reinterpret_cast<const uint2 *>(kin + cbase)[tid];
+      const uint32_t u[2] = {q.x, q.y};
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        dg[2 * h] = digit_of(u[h] & 0xffffu, shift, nbits);
+        dg[2 * h + 1] = digit_of(u[h] >> 16, shift, nbits);
       }
     }
   } else {
 #pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-      const uint64_t idx = cbase + (uint64_t)i * kSortThreads + tid;
+    for (int i = 0; i < ITEMS; ++i) {
+      const uint64_t idx = cbase + (uint64_t)i * NT + tid;
       dg[i] = idx < I ? digit_of((uint32_t)kin[idx], shift, nbits) : 0u;
     }
   }
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < kSortItems; ++i)
-    wave_hist_add<R>(s_cnt, dg[i], whole || cbase + (uint64_t)i * kSortThreads + tid < I, nbits);
+  for (int i = 0; i < ITEMS; ++i)
+    wave_hist_add<R>(s_cnt, dg[i], whole || cbase + (uint64_t)i * NT + tid < I, nbits);
   __syncthreads();
 #pragma unroll
-  for (int d = tid; d < R; d += kSortThreads)
+  for (int d = tid; d < R; d += NT)
     job.cnt[(size_t)d * (size_t)job.stride + chunk] = hist_total<R>(s_cnt, d);
 }
 
@@ -221,16 +234,17 @@ __global__ void __launch_bounds__(256) k_sort_scan(SortJob job, int pass) {
 
 // FEW: the digits' rows of cnt hold the chunks' counts (at most kFewChunks of
 // them), not the scanned starts.
-template <typename KeyT, int R, bool FEW>
-__global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int pass, int nbits,
+template <typename KeyT, int R, int NT, bool FEW>
+__global__ void __launch_bounds__(NT) k_sort_scatter(SortJob job, int pass, int nbits,
                                                                 const KeyT *__restrict__ kin,
                                                                 const uint32_t *__restrict__ vin,
                                                                 KeyT *__restrict__ kout,
                                                                 uint32_t *__restrict__ vout) {
-  constexpr int DP = R / kSortThreads;      // digits per thread, consecutive
-  __shared__ uint32_t s_wh[kSortWaves][R];  // per wave and digit: count, then local offset
+  constexpr int ITEMS = kSortChunk / NT, WAVES = NT / 64;
+  constexpr int DP = R > NT ? R / NT : 1;   // digits per thread, consecutive
+  __shared__ uint32_t s_wh[WAVES][R];  // per wave and digit: count, then local offset
   __shared__ uint32_t s_off[R];             // global position of local slot 0, per digit
-  __shared__ uint32_t s_csum[kSortWaves];
+  __shared__ uint32_t s_csum[WAVES];
   __shared__ KeyT s_key[kSortChunk];
   __shared__ uint32_t s_val[kSortChunk];
 
@@ -241,10 +255,13 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int 
   const uint64_t chunk = chunk_of(blockIdx.x, nchunks);
   const uint64_t cbase = chunk * kSortChunk;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const bool digits = tid * DP < R;   // (the first threads hold the digits)
   // global starts of this chunk's runs of the thread's digits
   uint32_t run_start[DP];
 #pragma unroll
   for (int q = 0; q < DP; ++q) {
+    run_start[q] = 0u;
+    if (!digits) continue;
     const uint32_t *row = job.cnt + (size_t)(tid * DP + q) * (size_t)job.stride;
     if constexpr (!FEW) {
       run_start[q] = row[chunk];   // (from the scan)
@@ -263,12 +280,12 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int 
       s_off[tid * DP + q] = all;   // (each thread reads its own digits back)
     }
   }
-  for (int i = tid; i < kSortWaves * R; i += kSortThreads) (&s_wh[0][0])[i] = 0u;
+  for (int i = tid; i < WAVES * R; i += NT) (&s_wh[0][0])[i] = 0u;
   if constexpr (FEW) {
     // plus the totals of the digits below
     uint32_t mine = 0;
 #pragma unroll
-    for (int q = 0; q < DP; ++q) mine += s_off[tid * DP + q];
+    for (int q = 0; q < DP; ++q) mine += digits ? s_off[tid * DP + q] : 0u;
     const uint32_t inc = wave_incl_add(mine);
     if (lane == 63) s_csum[wave] = inc;
     __syncthreads();
@@ -277,31 +294,31 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int 
 #pragma unroll
     for (int q = 0; q < DP; ++q) {
       run_start[q] += base;
-      base += s_off[tid * DP + q];
+      base += digits ? s_off[tid * DP + q] : 0u;
     }
   }
   __syncthreads();
 
-  // Items of the chunk: nv; lane l of wave w holds item w 1024 + 64 i + l
+  // Items of the chunk: nv; lane l of wave w holds item w 64 ITEMS + 64 i + l
   // as its i-th (out-of-range lanes read the last item and take no part).
   const uint32_t nv = (I - cbase) < (uint64_t)kSortChunk ? (uint32_t)(I - cbase) : (uint32_t)kSortChunk;
   const int shift = job.digit_bits * pass;
-  const uint32_t obase = (uint32_t)wave * (64 * kSortItems) + (uint32_t)lane;
+  const uint32_t obase = (uint32_t)wave * (64 * ITEMS) + (uint32_t)lane;
   const KeyT *kc = kin + cbase;
   const uint32_t *vc = vin + cbase;
-  uint32_t kx[kSortItems];   // the keys (widened)
-  uint32_t val[kSortItems];
-  uint32_t rank[kSortItems];
+  uint32_t kx[ITEMS];   // the keys (widened)
+  uint32_t val[ITEMS];
+  uint32_t rank[ITEMS];
   const uint64_t lanemask_lt = (1ull << lane) - 1ull;
   // item i of this lane exists iff 64 i < rem
   const int rem = (int)nv - (int)obase;
   if (nv == (uint32_t)kSortChunk) {
     const KeyT *kp = kc + obase;
 #pragma unroll
-    for (int i = 0; i < kSortItems; ++i) kx[i] = kp[64 * i];
+    for (int i = 0; i < ITEMS; ++i) kx[i] = kp[64 * i];
   } else {
 #pragma unroll
-    for (int i = 0; i < kSortItems; ++i) kx[i] = load_at(kc, min(obase + 64u * i, nv - 1u));
+    for (int i = 0; i < ITEMS; ++i) kx[i] = load_at(kc, min(obase + 64u * i, nv - 1u));
   }
   // Rank: lanes with the same digit are ranked by lane; the lowest of them
   // adds their number to the wave's counter of the digit and hands the old
@@ -312,9 +329,9 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int 
   // The leader lane and the rank among the peers (6 bits each) wait in the
   // upper half of a 16-bit key's register, or in a register of their own.
   constexpr bool kPack = sizeof(KeyT) == 2;
-  uint32_t lead[kPack ? 1 : kSortItems];
+  uint32_t lead[kPack ? 1 : ITEMS];
 #pragma unroll
-  for (int i = 0; i < kSortItems; ++i) {
+  for (int i = 0; i < ITEMS; ++i) {
     const bool valid = 64 * i < rem;
     const uint32_t d = digit_of(kx[i], shift, nbits);
     const uint64_t peers = match_digit(d, __ballot(valid), nbits);
@@ -327,7 +344,7 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int 
     else lead[i] = ld;
   }
 #pragma unroll
-  for (int i = 0; i < kSortItems; ++i) {
+  for (int i = 0; i < ITEMS; ++i) {
     const uint32_t ld = kPack ? kx[i] >> 16 : lead[kPack ? 0 : i];
     rank[i] = (uint32_t)__shfl(rank[i], (int)(ld & 63u), 64) + (ld >> 6);
   }
@@ -340,7 +357,7 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int 
   for (int q = 0; q < DP; ++q) {
     cnt[q] = 0;
 #pragma unroll
-    for (int k = 0; k < kSortWaves; ++k) cnt[q] += s_wh[k][tid * DP + q];
+    for (int k = 0; k < WAVES; ++k) cnt[q] += digits ? s_wh[k][tid * DP + q] : 0u;
     mine += cnt[q];
   }
   const uint32_t c = wave_incl_add(mine);
@@ -351,9 +368,10 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int 
 #pragma unroll
   for (int q = 0; q < DP; ++q) {
     const int d = tid * DP + q;
+    if (!digits) continue;
     uint32_t run = local_start;
 #pragma unroll
-    for (int k = 0; k < kSortWaves; ++k) {
+    for (int k = 0; k < WAVES; ++k) {
       const uint32_t v = s_wh[k][d];
       s_wh[k][d] = run;
       run += v;
@@ -371,13 +389,13 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int 
   if (nv == (uint32_t)kSortChunk) {
     const uint32_t *vp = vc + obase;
 #pragma unroll
-    for (int i = 0; i < kSortItems; ++i) val[i] = vp[64 * i];
+    for (int i = 0; i < ITEMS; ++i) val[i] = vp[64 * i];
   } else {
 #pragma unroll
-    for (int i = 0; i < kSortItems; ++i) val[i] = load_at(vc, min(obase + 64u * i, nv - 1u));
+    for (int i = 0; i < ITEMS; ++i) val[i] = load_at(vc, min(obase + 64u * i, nv - 1u));
   }
 #pragma unroll
-  for (int i = 0; i < kSortItems; ++i) {
+  for (int i = 0; i < ITEMS; ++i) {
     if (64 * i < rem) {
       uint32_t kk = kPack ? (kx[i] & 0xffffu) : kx[i];
       asm volatile("" : "+v"(kk));
@@ -388,7 +406,7 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(SortJob job, int 
   }
   __syncthreads();
 
-  for (int p = tid; p < (int)nv; p += kSortThreads) {
+  for (int p = tid; p < (int)nv; p += NT) {
     const KeyT k = s_key[p];
     const uint32_t pos = s_off[digit_of((uint32_t)k, shift, nbits)] + (uint32_t)p;
     if (pos < I) {  // always, when the counts match the emitted keys
@@ -409,18 +427,22 @@ static hipError_t sort_passes(const SortJob &job, int key_bits, int64_t blocks, 
     const int nbits = left < job.digit_bits ? left : job.digit_bits;
     const KeyT *kin = reinterpret_cast<const KeyT *>(keys[p & 1]);
     KeyT *kout = reinterpret_cast<KeyT *>(keys[(p + 1) & 1]);
-    hipLaunchKernelGGL((k_sort_count<KeyT, R>), dim3((uint32_t)blocks), dim3(kSortThreads), 0, s,
-                       job, p, nbits, kin);
+    const bool few = blocks <= kFewChunks, resident = blocks <= kResidentChunks;
+    const int nt = resident ? kSortThreadsFew : kSortThreads;
+    auto *count = resident ? k_sort_count<KeyT, R, kSortThreadsFew>
+                           : k_sort_count<KeyT, R, kSortThreads>;
+    hipLaunchKernelGGL(count, dim3((uint32_t)blocks), dim3(nt), 0, s, job, p, nbits, kin);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (blocks > kFewChunks) {
+    if (!few) {
       hipLaunchKernelGGL(k_sort_scan<R>, dim3(R), dim3(256), 0, s, job, p);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    auto *scatter = blocks > kFewChunks ? k_sort_scatter<KeyT, R, false>
-                                        : k_sort_scatter<KeyT, R, true>;
-    hipLaunchKernelGGL(scatter, dim3((uint32_t)blocks), dim3(kSortThreads), 0, s, job, p, nbits,
-                       kin, vals[p & 1], kout, vals[(p + 1) & 1]);
+    auto *scatter = few        ? k_sort_scatter<KeyT, R, kSortThreadsFew, true>
+                    : resident ? k_sort_scatter<KeyT, R, kSortThreadsFew, false>
+                               : k_sort_scatter<KeyT, R, kSortThreads, false>;
+    hipLaunchKernelGGL(scatter, dim3((uint32_t)blocks), dim3(nt), 0, s, job, p, nbits, kin,
+                       vals[p & 1], kout, vals[(p + 1) & 1]);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;
