@@ -9,8 +9,9 @@
 //    exact; pixel-centre rect -> tile rect -> instance count;
 //  * the affine Pluecker record for the rasterizer and the SH colour.
 // A one-workgroup launch then scans the workgroups' instance totals (the emit
-// launch adds them up itself where they are few), and the emit launch writes the (tile key, Gaussian index) instances with a
-// load-balanced loop and adds the radix-sort digit histograms of those
+// launch adds them up itself where they are few), and the emit launch writes
+// the (tile key, Gaussian index) instances with a load-balanced loop and adds
+// the radix-sort digit histograms of those
 // keys. No workgroup waits for another.
 //
 // Backward: a slot-parallel segmented reduction sums the per-instance
