@@ -956,10 +956,11 @@ __device__ __forceinline__ void seg_scan_step(uint32_t seg, float *v) {
   }
 }
 
-// The same step for finite values: the moved value times 1 or 0 is added by
-// one multiply-add with a DPP operand, a third of the instructions (and the
-// same sums: the product is exact). The values' last writers may be the two
-// instructions before (a DPP operand needs two wait states).
+// The same step where the running sums are finite: the moved value times 1 or
+// 0 is added by one multiply-add with a DPP operand, a third of the
+// instructions (and the same sums: the product is exact; an infinite sum times
+// 0 would be a NaN in another segment). The values' last writers may be the
+// two instructions before (a DPP operand needs two wait states).
 #define HTGS_SEG_FMAC(ctrl, v, take)                                                         \
   _Pragma("unroll") for (int k_ = 0; k_ < kPartialFloats; k_ += 4)                           \
     asm("s_nop 1\n\t"                                                                        \
@@ -1190,10 +1191,12 @@ __device__ __forceinline__ void scan_partials(const float *__restrict__ partials
     // last lane of row 0 / row 2 into rows 1 / 3, then lane 31 into rows
     // 2 and 3. Segments are runs of consecutive slots, so equal owners
     // mean one run; the fixed tree makes the sums deterministic.
-    float z = 0.f;   // NaN if any value is infinite or NaN
+    // (no sum over 64 lanes can overflow if a lane's magnitudes add up to less
+    // than 2^121; false for infinities and NaN)
+    float mag = 0.f;
 #pragma unroll
-    for (int k = 0; k < kPartialFloats; ++k) z = fmaf(pv[k], 0.f, z);
-    if (__ballot(z != 0.f) == 0ull) {
+    for (int k = 0; k < kPartialFloats; ++k) mag += fabsf(pv[k]);
+    if (__ballot(!(mag < 0x1p121f)) == 0ull) {
       seg_scan_step_finite<0x111, 0xf>(seg, pv);   // row_shr:1
       seg_scan_step_finite<0x112, 0xf>(seg, pv);   // row_shr:2
       seg_scan_step_finite<0x114, 0xf>(seg, pv);   // row_shr:4
