@@ -431,9 +431,10 @@ int forward_impl(const htgs_gaussians *g, const htgs_camera *cams, int32_t n_vie
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((e = run_front(g, vs, cfg, L, ws, s, partials))) return e;
   const Ws w = make_ws(ws, L);
+  KCfg k = make_kcfg(g, cfg, tiles);
+  if (cap == 0) k.cost_order = 0;   // without room for lists there is no tile order either
   StageTimer t(HTGS_STAGE_RASTER_FWD, s, 1, partials);
-  HIP_TRY(launch_raster_fwd(w, vs, make_kcfg(g, cfg, tiles), static_cast<float *>(state),
-                            w.vals[w.final_buf], s));
+  HIP_TRY(launch_raster_fwd(w, vs, k, static_cast<float *>(state), w.vals[w.final_buf], s));
   return HTGS_OK;
 }
 
