@@ -260,6 +260,7 @@ ViewSet make_views(const htgs_camera *cams, int32_t n_views, const htgs_config *
     P.tiles_y = (c.height + cfg->tile_h - 1) / cfg->tile_h;
     P.tile_base = (int32_t)tiles;
     P.z_near = c.z_near;
+    if (c.z_near < 0.f) vs.behind = 1;
     P.state_off = state_off;
     P.out_rgb = out_rgb ? out_rgb[v] : nullptr;
     P.grad_rgb = grad_rgb ? grad_rgb[v] : nullptr;

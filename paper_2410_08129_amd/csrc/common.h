@@ -75,6 +75,7 @@ struct ViewParams {
 struct ViewSet {
   int32_t n;
   int32_t total_tiles;
+  int32_t behind;       // a view lets splats through behind its camera (z_near < 0)
   ViewParams v[kMaxViews];
 };
 

@@ -511,9 +511,11 @@ __device__ __forceinline__ BatchInfo stage_batch(FwdLds<TW, TH, NBATCH> &L,
 }
 
 // Core keys: depth in the high word, list position and alpha slot in the
-// low word, as a double. Depths are positive and at most infinity (as
-// float32 bits, never a NaN of the double), so doubles compare like (depth,
-// position), and one minimum and one maximum per entry insert a fragment.
+// low word, as a double. Depths are below infinity (as float32 bits never a
+// NaN of the double), so doubles compare like (depth, position), and one
+// minimum and one maximum per entry insert a fragment. Of negative doubles the
+// larger low word is the smaller number: behind the camera (a negative z_near
+// lets such splats through) the position's bits are inverted.
 __device__ __forceinline__ double core_key(uint32_t hi, uint32_t lo) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
@@ -522,6 +524,13 @@ __device__ __forceinline__ uint32_t key_hi(double k) {
 }
 __device__ __forceinline__ uint32_t key_lo(double k) {
   return (uint32_t)(unsigned long long)__double_as_longlong(k);
+}
+// The list position of a key with SB slot bits (BEHIND: inverted where the
+// depth is negative).
+template <int SB, bool BEHIND>
+__device__ __forceinline__ uint32_t key_pos(double k) {
+  if constexpr (!BEHIND) return key_lo(k) >> SB;
+  return (key_lo(k) ^ (uint32_t)((int32_t)key_hi(k) >> 31)) >> SB;
 }
 // (fmin and fmax would canonicalize their operands first)
 __device__ __forceinline__ double key_min(double a, double b) {
@@ -561,13 +570,15 @@ __device__ __forceinline__ void add_fragments(const Ws &w, uint32_t n, int lane)
   if (lane == 0 && n) count_add(w.frags, (unsigned long long)n);
 }
 
-// One tile. EXACT: K == KMAX, known at compile time. Bound by VALU issue (93%
-// of the cycles on the 4K frame with K = 16: about 36 instructions per step of
-// the walk, 36 more where a lane inserts, 375 per staged batch) with 4.5 waves
-// per SIMD, which LDS sets. 1080p, K = 8, 8x8 tiles: 525 us when each block
+// One tile. EXACT: K == KMAX, known at compile time. BEHIND: a view has a
+// negative z_near, so that equal negative depths can meet (a test per insertion
+// instead took 1 to 4% of the launch). Bound by VALU issue (93% of the cycles on
+// the 4K frame with K = 16: about 36 instructions per step of the walk, 36 more
+// where a lane inserts, 375 per staged batch) with 4.5 waves per SIMD, which LDS
+// sets. 1080p, K = 8, 8x8 tiles: 525 us when each block
 // walked one list and shifted its core by compares and selects, 384 now; 4K
 // frame 8.30 -> 6.10 ms, 8 views 1180 -> 687 us.
-template <int KMAX, int TW, int TH, int BM, bool EXACT>
+template <int KMAX, int TW, int TH, int BM, bool EXACT, bool BEHIND>
 __device__ __forceinline__ void fwd_tile(const TileInfo &ti, const Ws &w, const ViewSet &vs,
                                          const KCfg &cfg, float *__restrict__ state,
                                          const uint32_t *__restrict__ vals) {
@@ -664,8 +675,9 @@ __device__ __forceinline__ void fwd_tile(const TileInfo &ti, const Ws &w, const 
         if (z < __uint_as_float(key_hi(key[KMAX - 1]))) {
           const uint32_t slot = key_lo(key[KMAX - 1]) & (uint32_t)(KMAX - 1);
           // row / kStageBytes for whole rows
-          const uint32_t pos = (base - rg.x) + ((off * 683u) >> 16);
+          uint32_t pos = (base - rg.x) + ((off * 683u) >> 16);
           my_alpha[slot * 64u] = alpha;
+          if constexpr (BEHIND) pos ^= (uint32_t)(__float_as_int(z) >> 31);
           core_insert<KMAX>(key, core_key(__float_as_uint(z), (pos << SB) | slot));
           far = __uint_as_float(key_hi(key[KMAX - 1])) + batch.reach;
         }
@@ -735,8 +747,9 @@ __device__ __forceinline__ void fwd_tile(const TileInfo &ti, const Ws &w, const 
     for (int i = 0; i < GR; ++i) {
       const bool got = i0 + i < K && key_hi(key[i0 + i]) != 0x7f800000u;
       const uint32_t lo = key_lo(key[i0 + i]);
-      pos[i] = got ? (int)(lo >> SB) : -1;
-      gids[i] = got ? (int)vals[rg.x + (lo >> SB)] : -1;
+      const uint32_t at = key_pos<SB, BEHIND>(key[i0 + i]);
+      pos[i] = got ? (int)at : -1;
+      gids[i] = got ? (int)vals[rg.x + at] : -1;
       ca[i] = got ? my_alpha[(lo & (uint32_t)(KMAX - 1)) * 64u] : 0.f;
     }
 #pragma unroll
@@ -1387,7 +1400,18 @@ __global__ void __launch_bounds__((TW * TH), (fwd_simd_waves<KMAX, TW, TH, BM>()
     k_raster_fwd(Ws w, ViewSet vs, KCfg cfg, float *__restrict__ state,
                  const uint32_t *__restrict__ vals) {
   TileInfo ti;
-  if (tile_info(vs, cfg, w, ti)) fwd_tile<KMAX, TW, TH, BM, EXACT>(ti, w, vs, cfg, state, vals);
+  if (tile_info(vs, cfg, w, ti))
+    fwd_tile<KMAX, TW, TH, BM, EXACT, false>(ti, w, vs, cfg, state, vals);
+}
+
+// Views with a negative z_near (any K up to KMAX).
+template <int KMAX, int TW, int TH>
+__global__ void __launch_bounds__(TW * TH)
+    k_raster_fwd_behind(Ws w, ViewSet vs, KCfg cfg, float *__restrict__ state,
+                        const uint32_t *__restrict__ vals) {
+  TileInfo ti;
+  if (tile_info(vs, cfg, w, ti))
+    fwd_tile<KMAX, TW, TH, 1, false, true>(ti, w, vs, cfg, state, vals);
 }
 
 template <int KMAX, int TW, int TH, bool WIDE, bool EXACT>
@@ -1689,6 +1713,10 @@ static hipError_t fwd_launch_bm(const Ws &w, const ViewSet &vs, const KCfg &cfg,
 template <int KMAX, int TW, int TH, bool EXACT>
 static hipError_t fwd_launch(const Ws &w, const ViewSet &vs, const KCfg &cfg, float *state,
                              const uint32_t *vals, hipStream_t s) {
+  if (vs.behind) {
+    hipLaunchKernelGGL((k_raster_fwd_behind<KMAX, TW, TH>), tile_grid(vs, cfg), dim3(TW * TH), 0, s, w, vs, cfg, state, vals);
+    return hipGetLastError();
+  }
   if constexpr (TW == 8) {
     if (cfg.batch_mult == 2) return fwd_launch_bm<KMAX, TW, TH, 2, EXACT>(w, vs, cfg, state, vals, s);
   }
