@@ -43,6 +43,9 @@ namespace htgs {
 
 typedef float float4v __attribute__((ext_vector_type(4)));   // one 16-byte LDS read
 typedef float float2v __attribute__((ext_vector_type(2)));
+// two 16-bit list entries in one read (the compiler may not move it past the
+// entries' stores)
+typedef uint32_t __attribute__((may_alias)) list_pair;
 typedef __attribute__((address_space(3))) const char *lds_bytes;   // a 32-bit LDS address
 typedef __attribute__((address_space(3))) const float2v *lds_float2;
 typedef __attribute__((address_space(3))) const float4v *lds_float4;
@@ -688,7 +691,7 @@ __device__ __forceinline__ void fwd_tile(const TileInfo &ti, const Ws &w, const 
     // times per round: 411 against 395 us for the launch at 1080p with K = 8);
     // the next round's rows are looked up meanwhile (the last look-up lies
     // past the list, inside L, and is not used).
-    const uint32_t *list = reinterpret_cast<const uint32_t *>(L.list[wave][lane / kPartLanes]);
+    const list_pair *list = reinterpret_cast<const list_pair *>(L.list[wave][lane / kPartLanes]);
     uint32_t next = list[0];
     for (int q = 0; q < batch.nlist; q += 2) {
       const uint32_t o = next;
@@ -873,7 +876,7 @@ __device__ __forceinline__ void fwd_tile_sorted(const TileInfo &ti, const Ws &w,
       ++nb;
       end_pos = pos + 1;
     };
-    const uint32_t *list = reinterpret_cast<const uint32_t *>(L.list[wave][lane / kPartLanes]);
+    const list_pair *list = reinterpret_cast<const list_pair *>(L.list[wave][lane / kPartLanes]);
     for (int q = 0; q < nlist && !done; q += 2) {
       const uint32_t o = list[q / 2];
       const StagedRow r0 = read_row(rows + (o & 0xffffu)), r1 = read_row(rows + (o >> 16));
