@@ -111,6 +111,27 @@ def settings_desc(st):
             "persistent": bool(st.persistent)}
 
 
+def instance_room(n, cams, st, ws_bytes):
+    """Instances that a workspace of ws_bytes has room for."""
+    from paper_2410_08129_amd import htgs
+    lo, hi = 0, 1 << 30
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        if htgs.workspace_bytes(n, cams, st, mid) <= ws_bytes:
+            lo = mid
+        else:
+            hi = mid
+    return lo
+
+
+def few_tiles(kmax, st, tiles, room):
+    """Whether the backward raster takes its form for few tiles (the rule of
+    few_tiles in csrc/raster.hip)."""
+    if kmax > 16 and st.tile_w * st.tile_h == 128 and tiles > 256:
+        return tiles <= 384 and room > (256 if tiles <= 320 else 1024) * tiles
+    return tiles <= 512 and room > 64 * tiles
+
+
 def tune(params, sc, cams, st, args):
     from paper_2410_08129_amd import autotune
     if args.tile_cull != "auto":
@@ -212,8 +233,8 @@ def run_single(args):
     kmax = next(k for k in (1, 2, 4, 8, 16, 32) if k >= max(st.K, 1))
     exact = "true" if st.K == kmax else "false"
     if dom == "raster_bwd":
-        # (the form for few tiles of long lists has "true" before the last argument)
-        few = tiles_x * tiles_y <= 512 and keys.size > 64 * tiles_x * tiles_y
+        # (the form for few tiles has "true" before the last argument)
+        few = few_tiles(kmax, st, tiles_x * tiles_y, instance_room(sc.n, [cam], st, ws.numel()))
         key = (f"k_raster_bwd<{kmax}, {st.tile_w}, {st.tile_h}, {'true' if few else 'false'}, "
                f"{exact}>")
     else:

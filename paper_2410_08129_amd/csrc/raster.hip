@@ -1051,8 +1051,10 @@ constexpr int bwd_waves() {
 // Target waves per SIMD of the backward (register budget; HIP's second
 // launch-bounds argument is a minimum number of waves per execution unit).
 // The walk of a one-block tile with K <= 8 fits 96 registers; at 80 it
-// spills (630 against 516 us at 1080p; now 488). Larger cores and tiles fit 128,
-// except where LDS allows no more than two or three waves anyway.
+// spills (630 against 516 us at 1080p; now 488). Tiles of several blocks with
+// K <= 8, and tiles of up to two with K <= 16, fit 128 (16x16 with one register
+// spilled); the others take 127 to 184, and LDS allows them no more
+// than two or three waves anyway.
 template <int KMAX, int TW, int TH>
 constexpr int bwd_simd_waves() {
   return (TW * TH <= 64 && KMAX <= 8) ? 5 : ((KMAX <= 8 || (KMAX <= 16 && TW * TH <= 128)) ? 4 : 1);
@@ -1726,21 +1728,36 @@ static hipError_t fwd_launch(const Ws &w, const ViewSet &vs, const KCfg &cfg, fl
   return fwd_launch_bm<KMAX, TW, TH, 1, EXACT>(w, vs, cfg, state, vals, s);
 }
 
-// Frames of up to this many tiles take the wide backward: two workgroups per
-// CU, which registers and LDS allow for every core size, so that all tiles run
-// at once. Past it the wide form loses where lists are short (1200 tiles of
-// 16x16, K = 8: 84 -> 119 us with 50k Gaussians, 216 -> 178 with 300k; 2048 of
-// 8x8 32 -> 42), below it wins where they are long (50k Gaussians, 192
-// tiles of 8x8 46 -> 22 us, 128 of 16x16 87 -> 62, 512 of 16x8 49 -> 35). With
-// room for less than a chunk per tile there is nothing to share.
-constexpr int kFewTiles = 512;
+// Frames of up to 512 tiles take the wide backward where there is room for more
+// than 64 instances per tile; with less there is nothing to share. (Room, not
+// the lists' length, which the host does not know: short lists in a roomy
+// workspace take 18.6 -> 20.4 us with 16x8 tiles and K = 16, within 0.5 us of
+// the other form with 8x8 or 16x16 tiles and K = 8.) Up to 128 VGPRs two
+// workgroups share a CU and all tiles run at once: 50k Gaussians, 256 and 504
+// tiles of 8x8 with K = 8 275 -> 88 and 230 -> 97 us, 16x8 with K = 16 261 -> 172
+// and 249 -> 207, 16x16 with K = 8 511 -> 304 and 450 -> 343; past 512 it loses
+// where lists are short (1200 tiles of 16x16, K = 8: 84 -> 119 us with 50k
+// Gaussians, 216 -> 178 with 300k; 2048 of 8x8 32 -> 42). The forms with more
+// registers (K > 16, and 8 < K <= 16 with tiles of 256 pixels but for 32x8 with
+// K = 16) run one workgroup per CU, 256 tiles at a time, and still win or draw
+// up to 512 tiles (50k Gaussians, 504 tiles of 8x8 with K = 32 264 -> 117, of
+// 16x16 with K = 12 478 -> 338, of 32x8 with K = 12 425 -> 415; with 5k 43 -> 37,
+// 92 -> 95, 91 -> 64), except 16x8 with K > 16, whose four pairs of waves share
+// less. K = 24 with 160, 300 to 350, 600 to 700 and 1500 to 1750 instances per
+// tile: 59 -> 71, 88 -> 86, 144 -> 119 and 324 -> 209 us at 272 tiles, 58 -> 73,
+// 85 -> 89, 146 -> 121 and 305 -> 236 at 304, 61 -> 75, 83 -> 91, 133 -> 148 and
+// 299 -> 266 at 384, 61 -> 75, 87 -> 91, 132 -> 148 and 287 -> 306 at 448.
+template <int KMAX, int TW, int TH>
 static bool few_tiles(const Ws &w, const ViewSet &vs) {
-  return vs.total_tiles <= kFewTiles && w.capacity > (int64_t)64 * vs.total_tiles;
+  const int64_t tiles = vs.total_tiles;
+  if (KMAX > 16 && TW * TH == 128 && tiles > 256)
+    return tiles <= 384 && w.capacity > (tiles <= 320 ? 256 : 1024) * tiles;
+  return tiles <= 512 && w.capacity > 64 * tiles;
 }
 template <int KMAX, int TW, int TH, bool EXACT>
 static hipError_t bwd_launch(const Ws &w, const ViewSet &vs, const KCfg &cfg, const float *state,
                              const uint32_t *vals, hipStream_t s) {
-  const bool wide = few_tiles(w, vs);
+  const bool wide = few_tiles<KMAX, TW, TH>(w, vs);
   auto *bwd = wide ? k_raster_bwd<KMAX, TW, TH, true, EXACT> : k_raster_bwd<KMAX, TW, TH, false, EXACT>;
   const int threads = 64 * (wide ? bwd_waves<TW, TH, true>() : bwd_waves<TW, TH, false>());
   hipLaunchKernelGGL(bwd, tile_grid(vs, cfg), dim3(threads), 0, s, w, vs, cfg, state, vals);
