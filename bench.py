@@ -111,6 +111,11 @@ def settings_desc(st):
             "persistent": bool(st.persistent)}
 
 
+def sort_passes(key_bits):
+    """Passes of the tile sort (sort_pass_count in csrc/common.h)."""
+    return {9: 1, 17: 2, 18: 2}.get(key_bits, (key_bits + 7) // 8)
+
+
 def instance_room(n, cams, st, ws_bytes):
     """Instances that a workspace of ws_bytes has room for."""
     from paper_2410_08129_amd import htgs
@@ -254,7 +259,7 @@ def run_single(args):
     # preprocess reads the parameters and writes record, rect and offset.
     n_tiles = tiles_x * tiles_y
     key_bits = max(1, (n_tiles - 1).bit_length())
-    passes = (key_bits + 7) // 8
+    passes = sort_passes(key_bits)
     kb = 2 if key_bits <= 16 else 4
     sort_bytes_pass = n_inst * 2 * (kb + 4)
     b_bin = 8 * sc.n + n_inst * ((kb + 4) + kb + 2 * passes * (kb + 4) + kb) + 8 * n_tiles

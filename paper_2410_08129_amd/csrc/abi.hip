@@ -375,6 +375,16 @@ Clear make_clear(void *ws, const Layout &L, bool count) {
           {(uint32_t)(L.pp_total / 16), count ? 0u : (uint32_t)((L.zero_end - second) / 16)}};
 }
 
+// Kernel launches of a radix sort in chunks (launch_sort_passes,
+// launch_depth_sort without its keys) and of the preprocess.
+int sort_launches(int passes, int64_t capacity) {
+  return passes * (few_chunks(capacity) ? 2 : 3);
+}
+int preprocess_launches(int64_t n, bool sorted) {
+  if (n == 0) return 0;
+  return 2 + (sorted ? 1 : 0) + ((n + kPreThreads - 1) / kPreThreads > kAddTotals ? 1 : 0);
+}
+
 // Whether the preprocess launch clears, which saves the launch of a fill (6 us
 // of a frame): not with a depth sort ahead of it, which needs its histograms
 // zero, nor where its threads would have to store more than 256 bytes each.
@@ -393,20 +403,20 @@ int run_front(const htgs_gaussians *g, const ViewSet &vs, const htgs_config *cfg
     clr.n[0] = clr.n[1] = 0u;
   }
   if (L.sorted) {
-    StageTimer t(HTGS_STAGE_DEPTH_SORT, s, 13, timed);
+    StageTimer t(HTGS_STAGE_DEPTH_SORT, s, g->n ? 1 + sort_launches(4, g->n) : 0, timed);
     HIP_TRY(launch_depth_sort(w, g->means, g->n, vs.v[0].w2c, s));
   }
   {
-    StageTimer t(HTGS_STAGE_PREPROCESS, s, 1, timed);
+    StageTimer t(HTGS_STAGE_PREPROCESS, s, preprocess_launches(g->n, L.sorted), timed);
     HIP_TRY(launch_preprocess(make_gp(g), make_kcfg(g, cfg, vs.total_tiles), vs, w,
                               clr, s));
   }
   if (L.capacity > 0) {
-    StageTimer t(HTGS_STAGE_SORT, s, 3 * L.passes, timed);
+    StageTimer t(HTGS_STAGE_SORT, s, sort_launches(L.passes, L.capacity), timed);
     HIP_TRY(launch_sort_passes(w, s));
   }
   if (L.capacity > 0) {
-    StageTimer t(HTGS_STAGE_RANGES, s, 1, timed);
+    StageTimer t(HTGS_STAGE_RANGES, s, cfg->flags & HTGS_FLAG_COST_ORDER ? 3 : 1, timed);
     HIP_TRY(launch_ranges(w, vs.total_tiles, s));
     if (cfg->flags & HTGS_FLAG_COST_ORDER) HIP_TRY(launch_tile_order(w, vs.total_tiles, s));
   }
@@ -471,7 +481,7 @@ int backward_impl(const htgs_gaussians *g, const htgs_camera *cams, int32_t n_vi
   // itself.
   const GradPtrs gr{grads->means, grads->log_scales, grads->quats, grads->opacity_logits,
                     grads->sh, grads->mean_grad_stat, grads->visible_count};
-  StageTimer t(HTGS_STAGE_PREPROCESS_BWD, s);
+  StageTimer t(HTGS_STAGE_PREPROCESS_BWD, s, g->n ? (L.sorted && cap > 0 ? 2 : 1) : 0);
   HIP_TRY(launch_preprocess_bwd(make_gp(g), gr, k, vs, w, s));
   return HTGS_OK;
 }
@@ -596,7 +606,7 @@ int htgs_count_instances(const htgs_gaussians *g, const htgs_camera *cams, int32
     clr.n[0] = 0u;
   }
   {
-    StageTimer t(HTGS_STAGE_PREPROCESS, s);
+    StageTimer t(HTGS_STAGE_PREPROCESS, s, g->n ? 2 : 0);
     HIP_TRY(launch_count(make_gp(g), make_kcfg(g, cfg, tiles), vs, make_ws(ws, L0), clr, s));
   }
   unsigned long long total = 0;

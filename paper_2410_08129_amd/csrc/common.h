@@ -27,6 +27,10 @@ constexpr int kResidentChunks = 512;
 // reads cost more than the launch.
 constexpr int kFewChunks = 64;
 constexpr int kPreThreads = 256;
+// Up to this many preprocess workgroups (262,144 Gaussians) the emit launch adds
+// their totals up itself: at most 8 KiB read per workgroup, in place of a
+// launch of one workgroup (about 5 us).
+constexpr int kAddTotals = 1024;
 
 // Raster record of one Gaussian in one view (float32). The Pluecker
 // direction d and moment m of the ray through a pixel are affine in the
@@ -131,7 +135,7 @@ struct Ws {
                                // kCflagVisible: the pixel rect is not empty
   void *keys[2];
   uint32_t *vals[2];
-  float *partials;             // [capacity][24]
+  float *partials;             // [capacity][kPartialFloats]
   // Sorted blending: the Gaussians' mean-depth sort keys, sorted (key,
   // index) pairs (ping-pong; the final index buffer is the order the
   // emit launch walks), its digit histograms and per-chunk counts.

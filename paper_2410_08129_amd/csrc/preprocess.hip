@@ -1544,11 +1544,6 @@ hipError_t launch_fill_zero(void *p, int64_t bytes, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Up to this many preprocess workgroups (262,144 Gaussians) the emit launch adds
-// their totals up itself: at most 8 KiB read per workgroup, in place of a
-// launch of one workgroup (about 5 us).
-constexpr int kAddTotals = 1024;
-
 hipError_t launch_preprocess(const GaussPtrs &gp, const KCfg &cfg, const ViewSet &vs, const Ws &w,
                              const Clear &clr, hipStream_t s) {
   if (cfg.n == 0) return hipSuccess;
