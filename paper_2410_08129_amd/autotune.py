@@ -21,7 +21,7 @@ from . import htgs
 
 CANDIDATES = (
     # (tile width, tile height, lds_batch multiplier, cost order, tile culling,
-    #  tile queue: without effect, its names stay known)
+    #  tile queue: without effect, so never tried)
     (8, 8, 1, False, False, False), (8, 8, 2, False, False, False),
     (8, 8, 1, True, False, False), (8, 8, 2, True, False, False),
     (16, 8, 1, False, False, False), (16, 16, 1, False, False, False),
@@ -30,9 +30,6 @@ CANDIDATES = (
     (16, 8, 1, False, True, False), (16, 8, 1, True, True, False),
     (16, 16, 1, False, True, False), (16, 16, 1, True, True, False),
     (32, 8, 1, False, True, False), (32, 8, 1, True, True, False),
-    (8, 8, 1, False, True, True), (8, 8, 1, True, True, True),
-    (16, 8, 1, False, True, True), (16, 8, 1, True, True, True),
-    (16, 16, 1, False, True, True), (16, 16, 1, True, True, True),
 )
 
 
@@ -43,7 +40,7 @@ def _cache_path():
 def _key(n, cams, st, sh_degree):
     px = sum(c.width * c.height for c in cams)
     dev = torch.cuda.get_device_name(0) if torch.cuda.is_available() else "cpu"
-    return (f"v4|{dev}|n{int(math.log2(max(n, 1)))}|px{int(math.log2(max(px, 1)))}|v{len(cams)}"
+    return (f"v5|{dev}|n{int(math.log2(max(n, 1)))}|px{int(math.log2(max(px, 1)))}|v{len(cams)}"
             f"|K{st.K}|sh{sh_degree}")
 
 
@@ -52,8 +49,14 @@ def candidate_name(cand):
             f"{'_cull' if cand[4] else ''}{'_queue' if cand[5] else ''}")
 
 
+# Schedules that once had a twin with a tile queue: the twin's name stays known.
+_QUEUE_NAMES = {candidate_name(c) + "_queue": c for c in CANDIDATES if c[4] and c[0] < 32}
+
+
 def by_name(name):
     """The candidate called ``name`` (as in the tuning reports)."""
+    if name in _QUEUE_NAMES:
+        return _QUEUE_NAMES[name]
     for cand in CANDIDATES:
         if candidate_name(cand) == name:
             return cand
