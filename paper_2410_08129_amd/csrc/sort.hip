@@ -241,7 +241,7 @@ __global__ void __launch_bounds__(NT) k_sort_scatter(SortJob job, int pass, int 
                                                                 KeyT *__restrict__ kout,
                                                                 uint32_t *__restrict__ vout) {
   constexpr int ITEMS = kSortChunk / NT, WAVES = NT / 64;
-  constexpr int DP = R > NT ? R / NT : 1;   // digits per thread, consecutive
+  static_assert(R <= NT, "a thread holds at most one digit");
   __shared__ uint32_t s_wh[WAVES][R];  // per wave and digit: count, then local offset
   __shared__ uint32_t s_off[R];             // global position of local slot 0, per digit
   __shared__ uint32_t s_csum[WAVES];
@@ -255,47 +255,34 @@ __global__ void __launch_bounds__(NT) k_sort_scatter(SortJob job, int pass, int 
   const uint64_t chunk = chunk_of(blockIdx.x, nchunks);
   const uint64_t cbase = chunk * kSortChunk;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const bool digits = tid * DP < R;   // (the first threads hold the digits)
-  // global starts of this chunk's runs of the thread's digits
-  uint32_t run_start[DP];
-#pragma unroll
-  for (int q = 0; q < DP; ++q) {
-    run_start[q] = 0u;
-    if (!digits) continue;
-    const uint32_t *row = job.cnt + (size_t)(tid * DP + q) * (size_t)job.stride;
+  const bool digit = tid < R;   // (the first threads hold a digit each)
+  // global start of this chunk's run of the thread's digit
+  uint32_t run_start = 0u;
+  uint32_t all = 0u;   // FEW: the digit's total
+  if (digit) {
+    const uint32_t *row = job.cnt + (size_t)tid * (size_t)job.stride;
     if constexpr (!FEW) {
-      run_start[q] = row[chunk];   // (from the scan)
+      run_start = row[chunk];   // (from the scan)
     } else {
-      uint32_t below = 0, all = 0;
       for (uint32_t c = 0; c < (uint32_t)nchunks; c += 4) {
         const uint4 a = *reinterpret_cast<const uint4 *>(row + c);
         const uint32_t u[4] = {a.x, a.y, a.z, a.w};
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
           all += c + h < (uint32_t)nchunks ? u[h] : 0u;
-          below += c + h < (uint32_t)chunk ? u[h] : 0u;
+          run_start += c + h < (uint32_t)chunk ? u[h] : 0u;
         }
       }
-      run_start[q] = below;
-      s_off[tid * DP + q] = all;   // (each thread reads its own digits back)
     }
   }
   for (int i = tid; i < WAVES * R; i += NT) (&s_wh[0][0])[i] = 0u;
   if constexpr (FEW) {
     // plus the totals of the digits below
-    uint32_t mine = 0;
-#pragma unroll
-    for (int q = 0; q < DP; ++q) mine += digits ? s_off[tid * DP + q] : 0u;
-    const uint32_t inc = wave_incl_add(mine);
+    const uint32_t inc = wave_incl_add(all);
     if (lane == 63) s_csum[wave] = inc;
     __syncthreads();
-    uint32_t base = inc - mine;
-    for (int k = 0; k < wave; ++k) base += s_csum[k];
-#pragma unroll
-    for (int q = 0; q < DP; ++q) {
-      run_start[q] += base;
-      base += digits ? s_off[tid * DP + q] : 0u;
-    }
+    run_start += inc - all;
+    for (int k = 0; k < wave; ++k) run_start += s_csum[k];
   }
   __syncthreads();
 
@@ -352,33 +339,24 @@ __global__ void __launch_bounds__(NT) k_sort_scatter(SortJob job, int pass, int 
 
   // Per digit: the chunk's count; the local start of each digit is the
   // exclusive scan of the counts over digits.
-  uint32_t cnt[DP], mine = 0;
+  uint32_t mine = 0;
 #pragma unroll
-  for (int q = 0; q < DP; ++q) {
-    cnt[q] = 0;
-#pragma unroll
-    for (int k = 0; k < WAVES; ++k) cnt[q] += digits ? s_wh[k][tid * DP + q] : 0u;
-    mine += cnt[q];
-  }
+  for (int k = 0; k < WAVES; ++k) mine += digit ? s_wh[k][tid] : 0u;
   const uint32_t c = wave_incl_add(mine);
   if (lane == 63) s_csum[wave] = c;
   __syncthreads();
   uint32_t local_start = c - mine;
   for (int k = 0; k < wave; ++k) local_start += s_csum[k];
-#pragma unroll
-  for (int q = 0; q < DP; ++q) {
-    const int d = tid * DP + q;
-    if (!digits) continue;
+  if (digit) {
     uint32_t run = local_start;
 #pragma unroll
     for (int k = 0; k < WAVES; ++k) {
-      const uint32_t v = s_wh[k][d];
-      s_wh[k][d] = run;
+      const uint32_t v = s_wh[k][tid];
+      s_wh[k][tid] = run;
       run += v;
     }
-    // position of local slot p of digit d: run_start + (p - local_start)
-    s_off[d] = run_start[q] - local_start;
-    local_start += cnt[q];
+    // position of local slot p of the digit: run_start + (p - local_start)
+    s_off[tid] = run_start - local_start;
   }
   __syncthreads();
 
