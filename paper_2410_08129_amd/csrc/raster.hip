@@ -33,6 +33,12 @@
 // partial per instance (the moments about the pixel at the centre of the
 // Gaussian's tile rect, opacity and colour terms): no floating-point
 // atomics, deterministic results.
+//
+// Launch times in the comments are HIP events around the launch over frames
+// rendered one after another into kept buffers, once the clocks are steady.
+// (The first few dozen steps after an idle time run 7% slower: a benchmark run
+// of 20 steps after 5 gives 411 and 520 us for the 1080p launches, one of 200
+// after 50 gives 382 and 491. Kernel tracing adds another 10%.)
 #include <float.h>
 
 #include <type_traits>
@@ -575,12 +581,14 @@ __device__ __forceinline__ void add_fragments(const Ws &w, uint32_t n, int lane)
 
 // One tile. EXACT: K == KMAX, known at compile time. BEHIND: a view has a
 // negative z_near, so that equal negative depths can meet (a test per insertion
-// instead took 1 to 4% of the launch). Bound by VALU issue (93% of the cycles on
-// the 4K frame with K = 16: about 36 instructions per step of the walk, 36 more
-// where a lane inserts, 375 per staged batch) with 4.5 waves per SIMD, which LDS
-// sets. 1080p, K = 8, 8x8 tiles: 525 us when each block
-// walked one list and shifted its core by compares and selects, 384 now; 4K
-// frame 8.30 -> 6.10 ms, 8 views 1180 -> 687 us.
+// instead took 1 to 4% of the launch). Bound by VALU issue: an instruction per
+// 3.5 cycles and SIMD at 1080p with K = 8 and per 3.8 on the 4K frame with K =
+// 16, where float32 arithmetic takes 2.7 cycles and compares, selects, integer
+// and float64 operations 4.4 (about 36 instructions per step of the walk, 36
+// more where a lane inserts, 375 per staged batch), with 4.5 waves per SIMD,
+// which LDS sets. 1080p, K = 8, 8x8 tiles: 525 us when each block walked one list
+// and shifted its core by compares and selects, 384 now; 4K frame 8.30 -> 6.10
+// ms, 8 views 1180 -> 687 us.
 template <int KMAX, int TW, int TH, int BM, bool EXACT, bool BEHIND>
 __device__ __forceinline__ void fwd_tile(const TileInfo &ti, const Ws &w, const ViewSet &vs,
                                          const KCfg &cfg, float *__restrict__ state,
@@ -1065,11 +1073,12 @@ constexpr int bwd_simd_waves() {
 // out: 143 of them for 0.42 GB of partials in random 64-byte slots, 40 for a
 // 16-byte descriptor in a random line per instance, the rest 0.45 GB of state
 // and 0.85 GB of records) to 488 us; on the 4K frame (K = 16) 5.6 of 7.4 ms
-// remain without it. The launch took 602 us with a branch per fragment that
-// formed the code table's addresses lane by lane, tested the clamp and the
-// smallest |d|^2 for every pixel and wrote 64 scattered partials per store,
-// and 514 before the state and the partials became non-temporal; K = 16
-// with 16x8 tiles 941 -> 690 us, the 4K frame 8.83 -> 7.40 ms.
+// remain without it. A SIMD issues an instruction per 3.5 cycles on both. The
+// launch took 602 us with a branch per fragment that formed the code table's
+// addresses lane by lane, tested the clamp and the smallest |d|^2 for every
+// pixel and wrote 64 scattered partials per store, and 514 before the state and
+// the partials became non-temporal; K = 16 with 16x8 tiles 941 -> 690 us, the 4K
+// frame 8.83 -> 7.40 ms.
 template <int KMAX, int TW, int TH, bool WIDE, bool EXACT>
 __device__ __forceinline__ void bwd_tile(const TileInfo &ti, const Ws &w, const ViewSet &vs,
                                          const KCfg &cfg, const float *__restrict__ state,
